@@ -2707,7 +2707,7 @@ __device__ __forceinline__ void lanegroup_transpose4(unsigned& r0, unsigned& r1,
 // LDS layout of legendre_rmma_kernel (bytes), shared with the host.
 struct RmLayout {
   int nb, ncol, pld, bld;
-  size_t o_p, o_d, o_b, o_c, o_s, total, pplane, bplane;
+  size_t o_p, o_d, o_b, o_c, o_s, o_z, total, pplane, bplane;
 };
 __host__ __device__ inline RmLayout rm_layout(int L, int h, int nt, int nw, int es, int planes) {
   RmLayout q;
@@ -2728,6 +2728,7 @@ __host__ __device__ inline RmLayout rm_layout(int L, int h, int nt, int nw, int 
   q.o_b = take(q.bplane * planes * es);
   q.o_c = take(sizeof(double) * (32 * q.nb + 1));
   q.o_s = take(sizeof(double) * 2 * 8 * nt * 16);  // the block's gamma^2 h_l per parity, item, row
+  q.o_z = take(sizeof(double) * nw * q.ncol);      // float: the waves' degree-0 sums (order 0)
   q.total = off;
   return q;
 }
@@ -2833,6 +2834,25 @@ legendre_rmma_kernel(LegArgs<T> A) {
     for (int s = 0; s < NKS; ++s)
 #pragma unroll
       for (int par = 0; par < 2; ++par) yb[s][par][t] = TR::make(xv[s][par]);
+  }
+  // Degree 0 in float64: R_0^0 is one number for every latitude, so f_00 is that
+  // times the sum of E.  Its error is the same at every point of the output, an
+  // offset of the kernel itself, to which solves with a small kernel ratio are
+  // sensitive (gradient of 8 pairs at 360x720, worst of 6 inputs: error against
+  // float64 2.0e-5 with f_00 from the float32 products).
+  double* zs = reinterpret_cast<double*>(smem_raw + Q.o_z);
+  if constexpr (OP == RM_F32) {
+    if (m == 0) {
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        double z = 0.0, lo, hi;
+#pragma unroll
+        for (int s = 0; s < NKS; ++s) z += (double)yb[s][0][t].v;
+        lane_pair16(z, lo, hi);
+        lane_pair32(lo + hi, lo, hi);
+        if (lg == 0) zs[wave * Q.ncol + 16 * t + li] = lo + hi;
+      }
+    }
   }
   __syncthreads();  // the coefficients are staged
 
@@ -2961,6 +2981,11 @@ legendre_rmma_kernel(LegArgs<T> A) {
       float o[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) o[e] = (float)((double)sum[e] * sc[e]);
+      if (OP == RM_F32 && m == 0 && r0 == 0 && par == 0 && q4 == 0) {
+        double z = 0.0;
+        for (int w = 0; w < nw; ++w) z += zs[w * NC + n];
+        o[0] = (float)(z * A.rseed[0] * sc[0]);
+      }
       TR::put4(Bs, Q.bplane, (size_t)(par * NC + n) * Q.bld + 4 * q4, o);
     }
     __syncthreads();
