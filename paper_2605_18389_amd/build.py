@@ -27,10 +27,12 @@ SOURCES = [
     ("host_math.cpp", False),
     ("api.cpp", True),
     ("kernels.hip", True),
+    ("rows_wave.hip", True),
 ]
 
 
-HASHED = ["api.cpp", "host_math.cpp", "host_math.h", "shot_internal.h", "kernels.hip"]
+HASHED = ["api.cpp", "host_math.cpp", "host_math.h", "shot_internal.h", "device_common.h", "kernels.hip",
+          "rows_wave.hip"]
 
 
 def source_hash():

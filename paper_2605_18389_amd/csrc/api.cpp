@@ -46,6 +46,7 @@ struct GridRec {
   std::vector<double> x, w;
   std::vector<double> aw_host;  // area weight of each row pair, double precision
   std::vector<int> fac;
+  RingDev* d_rowfft = nullptr;       // latitude-longitude grids: the row length's radices
   int tab_kind = TAB_F32;
   void* d_tab = nullptr;
   int* d_morder = nullptr;           // [L] order run by MFMA workgroup column b (rows balanced over units)
@@ -217,11 +218,12 @@ uint16_t to_bf16(double v) {
 void free_grid(GridRec& g) {
   for (void* p : {g.d_tab, (void*)g.d_xs, (void*)g.d_rcoef, (void*)g.d_rgam,
                   (void*)g.d_rseed, (void*)g.sw.d_parts, (void*)g.sw.d_ck, (void*)g.ss.d_parts,
-                  (void*)g.ss.d_ck, (void*)g.d_morder, (void*)g.d_ring, (void*)g.d_rpair, g.d_ring_tw, g.d_ring_ph, g.d_ring_blu, (void*)g.d_cut, g.d_pbuf, g.d_aw, g.d_tw})
+                  (void*)g.ss.d_ck, (void*)g.d_morder, (void*)g.d_rowfft, (void*)g.d_ring, (void*)g.d_rpair, g.d_ring_tw, g.d_ring_ph, g.d_ring_blu, (void*)g.d_cut, g.d_pbuf, g.d_aw, g.d_tw})
     if (p) (void)hipFree(p);
   g.d_tab = g.d_aw = g.d_tw = g.d_pbuf = g.d_ring_tw = g.d_ring_ph = g.d_ring_blu = nullptr;
   g.d_morder = nullptr;
   g.d_ring = nullptr;
+  g.d_rowfft = nullptr;
   g.d_rpair = nullptr;
   g.d_xs = g.d_rcoef = g.d_rgam = g.d_rseed = nullptr;
   g.sw = SplitSched{};
@@ -250,6 +252,17 @@ shot_status build_grid(shot_plan_s* P, GridRec& g, int leg_mode, hipStream_t s) 
   // table rows padded to the matrix-core K step (32) for fp32/bf16 tables
   g.hpad = P->prec == SHOT_FP64 ? (g.h + 3) / 4 * 4 : (g.h + 31) / 32 * 32;
   g.fac = g.hp ? std::vector<int>() : fft_factors(d.nlon);
+  if (!g.hp) {
+    RingDev R{};
+    const std::vector<int> f = fft_factors_wide(d.nlon), mg = fft_stage_magic(f);
+    if ((int)f.size() > RING_MAXFAC) return SHOT_E_UNSUPPORTED;
+    R.len = d.nlon;
+    R.nfac = (int)f.size();
+    std::copy(f.begin(), f.end(), R.fac);
+    std::copy(mg.begin(), mg.end(), R.mg);
+    const shot_status sr = upload((void**)&g.d_rowfft, std::vector<RingDev>{R}, s);
+    if (sr != SHOT_OK) return sr;
+  }
   const bool f64 = P->prec == SHOT_FP64;
   // area weights of rows 0..h-1 and twiddles in field precision
   std::vector<double> aw(g.h);
@@ -284,7 +297,11 @@ shot_status build_grid(shot_plan_s* P, GridRec& g, int leg_mode, hipStream_t s) 
       const std::vector<int> f = fft_factors(len);
       if ((int)f.size() > RING_MAXFAC) return SHOT_E_UNSUPPORTED;
       R.nfac = (int)f.size();
-      for (int q = 0; q < RING_MAXFAC; ++q) R.fac[q] = q < R.nfac ? f[q] : 0;
+      const std::vector<int> mg = fft_stage_magic(f);
+      for (int q = 0; q < RING_MAXFAC; ++q) {
+        R.fac[q] = q < R.nfac ? f[q] : 0;
+        R.mg[q] = q < R.nfac ? mg[q] : 0;
+      }
       // a prime factor above 64 (polar rings of 4p pixels beyond Nside 64):
       // Bluestein, a cyclic convolution of power-of-two length M >= 2 len - 1
       R.bm = 0;
@@ -688,6 +705,8 @@ RowArgs<T> row_args(const shot_plan_s* P, const GridRec& g, const Layout& Lo, co
   a.hs = Lo.hs;
   a.nfac = (int)g.fac.size();
   for (int i = 0; i < a.nfac && i < 8; ++i) a.fac[i] = g.fac[i];
+  a.rowfft = g.d_rowfft;
+  a.max_prime = g.fac.empty() ? 0 : *std::max_element(g.fac.begin(), g.fac.end());
   a.tw = static_cast<const cpx<T>*>(g.d_tw);
   a.aw = static_cast<const T*>(g.d_aw);
   if (g.hp) {

@@ -138,6 +138,38 @@ std::vector<int> fft_factors(int n) {
   return f;
 }
 
+std::vector<int> fft_factors_wide(int n) {
+  // powers of two as 8s and 4s: a row of 512 points or more keeps a wave's 64
+  // lanes busy with radix 8; shorter rows take 4s, a lone 4 and 2 become an 8
+  std::vector<int> f;
+  int twos = 0, m = n;
+  while (m > 0 && m % 2 == 0) {
+    m /= 2;
+    ++twos;
+  }
+  while (twos >= 3 && (n >= 512 || twos == 3)) {
+    f.push_back(8);
+    twos -= 3;
+  }
+  while (twos >= 2) {
+    f.push_back(4);
+    twos -= 2;
+  }
+  if (twos) f.push_back(2);
+  for (int p : fft_factors(m)) f.push_back(p);
+  return f;
+}
+
+std::vector<int> fft_stage_magic(const std::vector<int>& f) {
+  std::vector<int> mg;
+  int ns = 1;
+  for (int r : f) {
+    mg.push_back(((1 << 20) + ns - 1) / ns);
+    ns *= r;
+  }
+  return mg;
+}
+
 void fft_pow2(std::vector<double>& re, std::vector<double>& im, int sign) {
   const size_t n = re.size();
   for (size_t i = 1, j = 0; i < n; ++i) {  // bit reversal

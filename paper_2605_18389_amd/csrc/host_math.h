@@ -48,6 +48,12 @@ void clenshaw_curtis(int n, std::vector<double>& x, std::vector<double>& w);
 // primes in increasing order (the device FFT runs those as generic stages).
 std::vector<int> fft_factors(int n);
 
+// Radices of the same length with powers of two taken as 8s and 4s (at most as
+// many factors as fft_factors), and each stage's ceil(2^20 / Ns), Ns the product
+// of the radices before it: b / Ns = b * magic >> 20 for b * Ns < 2^20.
+std::vector<int> fft_factors_wide(int n);
+std::vector<int> fft_stage_magic(const std::vector<int>& f);
+
 // In-place radix-2 FFT of a power-of-two length in double precision:
 // a[k] <- sum_n a[n] exp(sign 2 pi i n k / n_len) (no scaling).
 void fft_pow2(std::vector<double>& re, std::vector<double>& im, int sign);

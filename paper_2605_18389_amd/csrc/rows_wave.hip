@@ -1,10 +1,10 @@
 // Row kernels of many row pairs: TP threads of one wave per mirror pair.
 //
-// A launch of a batch has thousands of row pairs, and what bounds the
-// workgroup-per-group form (row_sink_kernel, row_kernel) there is instruction
-// issue and barriers: every FFT stage ends in a workgroup barrier, a stage of
-// a 720-point row keeps 60 % of 256 threads busy, and the pointwise step of
-// Alg. 1 costs an LDS round trip of its own.  Here a pair belongs to TP lanes
+// A launch of a batch has thousands of row pairs, and what bounded the
+// workgroup-per-group form (row_sink_kernel, row_kernel) there was instruction
+// issue and barriers: every FFT stage ended in a workgroup barrier, a stage of
+// a 720-point row kept 60 % of 256 threads busy, and the pointwise step of
+// Alg. 1 cost an LDS round trip of its own.  Here a pair belongs to TP lanes
 // of one wave, so its FFT stages need no barrier (LDS operations of a wave
 // complete in order), and
 //   * compile-time lengths: stages of radix 4 to 15 (composite radices of
@@ -20,6 +20,12 @@
 // workgroup, NP neighbouring pairs (16 NP bytes) of one order per run.
 // Arithmetic, partial sums and their slots are those of row_kernel; a wave
 // writes its sums at its first pair and the neutral element at the others.
+// Measured per launch (before -> after): Sinkhorn half of 24 items at 360x720
+// 41 -> 32 us (75 MB, 2.4 TB/s), reverse half of 16 items 46 -> 33 us, heat
+// apply rows of 16 items 21 + 28 -> 14 + 11 us; 24 HEALPix items at Nside 64
+// 56 -> 24 us, 4 at Nside 256 161 -> 65 us; one float64 item of 256-point rows
+// 12.8 -> 7.8 us.  What bounds it now: issue (about 3000 instructions per
+// 720-point pair) in batches, the launch's own latency for single items.
 
 #include <algorithm>
 

@@ -40,6 +40,7 @@ struct RingDev {
   int twoff;               // offset of this length's twiddles exp(-2 pi i k/len) in ring_tw
   int nfac;                // factors of len (4, 2, 3, 5, then other primes)
   int fac[RING_MAXFAC];
+  int mg[RING_MAXFAC];     // ceil(2^20 / product of the factors before): division by it
   // Bluestein transform for lengths with a large prime factor (bm > 0): the
   // length-len DFT as a cyclic convolution of power-of-two length bm
   int bm;                  // convolution length (0: direct stages)
@@ -79,6 +80,11 @@ struct RowArgs {
   const T* aw;        // h area weights (rows 0..h-1)
   int item0;          // absolute index of this launch's first item
   const ItemDev* items;
+  // row_wave_kernel: one entry with the radices of a latitude-longitude grid's
+  // rows (8s and 4s, then 2, 3, 5, other primes); LDS entries of a buffer
+  const RingDev* rowfft;
+  int wstride;
+  int max_prime;      // largest prime factor of a latitude-longitude grid's row length
   const int* rpair;   // ring grids: ring pair run by workgroup column b (nullptr: xcd_row_pair order)
   cpx<T>* spec;
   int mode;
@@ -169,8 +175,19 @@ struct LegArgs {
 // Launchers (kernels.hip).  All enqueue on `stream` and return the launch status.
 // set_launch_events: time the next row/Legendre launch with these events.
 void set_launch_events(hipEvent_t start, hipEvent_t stop);
+bool take_launch_events(hipEvent_t* start, hipEvent_t* stop);
 template <typename T>
 hipError_t launch_rows(const RowArgs<T>& a, int nb, hipStream_t stream);
+// Wave-per-pair row kernel (rows_wave.hip): the shape a launch takes (tp = 0:
+// not this kernel), ct: compile-time row length, tp lanes per pair, np pairs
+// per workgroup (run-time lengths).
+struct RowWaveShape {
+  int ct, tp, np;
+};
+template <typename T>
+RowWaveShape row_wave_shape(const RowArgs<T>& a, int nb);
+template <typename T>
+hipError_t launch_rows_wave(const RowArgs<T>& a, int nb, const RowWaveShape& w, hipStream_t stream);
 template <typename T>
 hipError_t launch_legendre(const LegArgs<T>& a, int table_kind, int ib, hipStream_t stream);
 int recur_jpt(int h);
