@@ -28,11 +28,12 @@ SOURCES = [
     ("api.cpp", True),
     ("kernels.hip", True),
     ("rows_wave.hip", True),
+    ("legendre64.hip", True),
 ]
 
 
 HASHED = ["api.cpp", "host_math.cpp", "host_math.h", "shot_internal.h", "device_common.h", "kernels.hip",
-          "rows_wave.hip"]
+          "rows_wave.hip", "legendre64.hip"]
 
 
 def source_hash():

@@ -809,6 +809,10 @@ int mma_tiles(const shot_plan_s* P, const GridRec& g, int count) {
   // Matrix cores for any item count: they stream the table faster than the
   // VALU table kernel even for a single item (one item at L = 720: bf16
   // 0.58 -> 0.12 ms per launch, fp32 0.80 -> 0.53 ms)
+  // float32 tables of up to 512 latitude pairs run the single-pass kernel (8
+  // items per workgroup whatever the tuned tile count)
+  if (g.tab_kind == TAB_F32 && g.h <= 512 && rmma_lds_bytes(g.d.L, g.h, 1, RM_F32) <= 160 * 1024)
+    return nt > 0 ? nt : 1;
   if (nt == 0) nt = count >= 32 ? 4 : (count >= 16 ? 2 : 1);
   // fewer column tiles while they overflow 60 KiB of LDS (several workgroups
   // per compute unit); one tile may take up to 150 KiB (fp32 tables of long
@@ -843,6 +847,13 @@ int split_ib(const shot_plan_s* P, const GridRec& g, int count) {
   return ib;
 }
 
+// Matrix-core kernel of float64 tables: unless a tuning asks for the VALU
+// kernel (chains -1, or items per workgroup), for any number of items (one item
+// at 721x1440 streams the table once instead of twice).
+bool use_t64(const GridRec& g) {
+  return g.tab_kind == TAB_F64 && g.d_tab != nullptr && g.tune_jpt == 0 && g.tune_ib == 0 && t64_fits(g.h);
+}
+
 template <typename T>
 shot_status run_rows(shot_plan_s* P, const RowArgs<T>& a, int nb, hipStream_t s) {
   ProfScope ps(P, s, 1);
@@ -866,7 +877,15 @@ shot_status run_leg(shot_plan_s* P, const GridRec& g, LegArgs<T> a, hipStream_t 
   int ib = 1, op = 0;
   const int nt = mma_tiles(P, g, a.nb);
   const int rnt = rmma_tiles(P, g, a.nb, a.mode, &op);
-  if (nt > 0) {
+  bool done = false;
+  if constexpr (sizeof(T) == 8) {
+    if (use_t64(g)) {
+      e = launch_legendre_t64(a, s);
+      done = true;
+    }
+  }
+  if (done) {
+  } else if (nt > 0) {
     e = launch_legendre_mma<T>(a, g.tab_kind, nt, s);
   } else if (rnt > 0) {
     e = launch_legendre_rmma<T>(a, op, rnt, s);
@@ -1283,6 +1302,7 @@ shot_status autotune_impl(shot_plan_s* P, GridRec& g, const Layout& Lo, int nite
       cand.push_back({ib, -1});  // VALU table kernel
     }
   }
+  if (g.tab_kind == TAB_F64 && t64_fits(g.h)) cand.push_back({0, 0});  // matrix cores
   if (mma_table(g))
     for (int nt : {1, 2, 4})
       if (16 * nt <= 2 * std::max(nitems, 8)) cand.push_back({0, nt});
@@ -1308,6 +1328,8 @@ shot_status autotune_impl(shot_plan_s* P, GridRec& g, const Layout& Lo, int nite
       if (rmma_tiles(P, g, nitems, 0, nullptr) != c.first / 8) continue;  // does not fit LDS
     } else if (g.tab_kind != TAB_RECUR && c.second > 0) {
       if (mma_tiles(P, g, nitems) != c.second) continue;  // does not fit LDS
+    } else if (use_t64(g)) {
+      // (fits: checked when the candidate was listed)
     } else if (use_split(P, g) ? split_ib(P, g, nitems) != c.first : pick_ib(P, g, nitems) != c.first) {
       continue;  // does not fit LDS
     }

@@ -622,4 +622,20 @@ __device__ void kratio_fold(const RowArgs<T>& A, int it, int k, int slot, double
   }
 }
 
+// Row (m, l = m) of the packed (m, l) triangle.
+__device__ __forceinline__ long long tri_off(long long m, long long L) { return m * L - m * (m - 1) / 2; }
+
+// 4 x 4 exchange of lane groups: afterwards register t holds, in lane group g,
+// what lane group t held in register g (lane groups = 16-lane rows).
+__device__ __forceinline__ void lanegroup_transpose4(unsigned& r0, unsigned& r1, unsigned& r2, unsigned& r3) {
+  auto a = __builtin_amdgcn_permlane32_swap(r0, r2, false, false);
+  auto b = __builtin_amdgcn_permlane32_swap(r1, r3, false, false);
+  auto c = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
+  auto d = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+  r0 = c[0];
+  r1 = c[1];
+  r2 = d[0];
+  r3 = d[1];
+}
+
 }  // namespace shot

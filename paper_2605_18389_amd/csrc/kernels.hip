@@ -849,7 +849,6 @@ __global__ void __launch_bounds__(BS) row_sink_kernel(RowArgs<T> A) {
 // ---------------------------------------------------------------------------
 // Legendre kernels.  grid = (L orders, item chunks), block = 256.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ long long tri_off(long long m, long long L) { return m * L - m * (m - 1) / 2; }
 
 template <typename TT>
 __device__ __forceinline__ auto tab_load(const TT* p) {
@@ -1536,7 +1535,8 @@ __global__ void __launch_bounds__(256, IB * C > 6 ? 2 : 3) legendre_split_kernel
 }
 
 // ---------------------------------------------------------------------------
-// Batched Legendre stage as matrix-core GEMMs (table plans, many items).
+// Batched Legendre stage as matrix-core GEMMs (bfloat16 tables, and float
+// tables beyond 512 latitude pairs).
 //
 // Per order m and parity, with columns n = (item, re/im) of the workgroup:
 //   analysis   D[r][n] = sum_j P̄[r][j] Y[j][n]       (A = table rows, K = j)
@@ -1782,7 +1782,9 @@ __global__ void __launch_bounds__(64 * NW) legendre_mma_kernel(LegArgs<T> A) {
 }
 
 // ---------------------------------------------------------------------------
-// Single-item table Legendre stage of a heat apply on the vector units.  For
+// Single-item table Legendre stage on the vector units (a heat apply; float
+// tables also run the analysis and the synthesis alone: 721x1440 207 -> 78 and
+// 84 -> 75 us against the matrix-core kernel with 2 of 16 columns in use).  For
 // one item the contractions are matrix-vector products bound by the table
 // stream, so each table element is read once and used for both:
 //   analysis   f_r = sum_j P_r(x_j) y_j     lane partials over the lane's 8
@@ -1832,7 +1834,7 @@ __host__ __device__ constexpr int gemv_waves() { return 8; }
 __host__ __device__ constexpr int gemv_rows() { return 4; }
 size_t gemv_lds_bytes() { return (size_t)gemv_waves() * (16 + 512 * 2) * sizeof(float); }
 
-template <typename T, typename TT, int NW, int RT>
+template <typename T, typename TT, int NW, int RT, int MODE>
 __global__ void __launch_bounds__(64 * NW) legendre_gemv_kernel(LegArgs<T> A) {
   static_assert(RT == 4 || RT == 8, "tiles of 4 or 8 rows");
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -1853,12 +1855,13 @@ __global__ void __launch_bounds__(64 * NW) legendre_gemv_kernel(LegArgs<T> A) {
   for (int e = 0; e < 8; ++e) {
     const int j = j0 + e;
     cpx<T> y{0, 0};
-    if (j < h) y = sp[2 * j];
+    if (MODE != 2 && j < h) y = sp[2 * j];
     yr[e] = (float)y.x;
     yi[e] = (float)y.y;
     gr[e] = gi[e] = 0.f;
   }
   float* bw = bw_all + wave * 16;
+  cpx<T>* cf = MODE == 0 ? nullptr : A.coeff + it.coff + tri_off(m, L);  // this order's coefficients
   auto load_tile = [&](GemvRow<TT> (&P)[RT], int t) {
 #pragma unroll
     for (int rr = 0; rr < RT; ++rr) {
@@ -1869,6 +1872,7 @@ __global__ void __launch_bounds__(64 * NW) legendre_gemv_kernel(LegArgs<T> A) {
   GemvRow<TT> P[RT];
   for (int t = wave >> 1; t * RT < npar; t += NW / 2) {
     load_tile(P, t);
+    if constexpr (MODE != 2) {
     // lane partials: value k = 2 rr + c
     float v[2 * RT];
 #pragma unroll
@@ -1905,8 +1909,14 @@ __global__ void __launch_bounds__(64 * NW) legendre_gemv_kernel(LegArgs<T> A) {
     constexpr int SHV = RT == 8 ? 2 : 3;
     if ((lane & ((1 << SHV) - 1)) == 0) {
       const int k = lane >> SHV, rp = t * RT + (k >> 1);
-      bw[k] = rp < npar ? z * (float)hl[2 * rp + par] : 0.f;
+      if constexpr (MODE == 0) bw[k] = rp < npar ? z * (float)hl[2 * rp + par] : 0.f;
+      else if (rp < npar) reinterpret_cast<T*>(cf + 2 * rp + par)[k & 1] = (T)z;
     }
+    } else if (lane < 2 * RT) {  // the coefficients of these rows are b
+      const int rp = t * RT + (lane >> 1);
+      bw[lane] = rp < npar ? (float)reinterpret_cast<const T*>(cf + 2 * rp + par)[lane & 1] : 0.f;
+    }
+    if constexpr (MODE == 1) continue;
     __builtin_amdgcn_wave_barrier();
     float b[2 * RT];
 #pragma unroll
@@ -1927,6 +1937,7 @@ __global__ void __launch_bounds__(64 * NW) legendre_gemv_kernel(LegArgs<T> A) {
         gi[e] = fmaf(pv, b[2 * rr + 1], gi[e]);
       }
   }
+  if constexpr (MODE == 1) return;
   // partial G of this wave, then the sum over the waves of each parity
   if (lok) {
     float4* g4 = reinterpret_cast<float4*>(gs + ((size_t)wave * 512 + j0) * 2);
@@ -1948,7 +1959,13 @@ __global__ void __launch_bounds__(64 * NW) legendre_gemv_kernel(LegArgs<T> A) {
 }
 
 // ---------------------------------------------------------------------------
-// Recurrence-fed matrix-core Legendre kernel (float32 fields, batches).
+// Matrix-core Legendre kernel (float32 fields, batches): recurrence-fed, or
+// (SRC == RM_TABLE, float32 tables) fed from the table, which it reads once for
+// both transforms; the table form also runs the analysis and the synthesis
+// alone (modes 1 and 2).  Table form against the two-pass legendre_mma_kernel
+// it replaces, heat apply at 360x720: 16 items 138 -> 42 us, 48 items 383 -> 90
+// us; 3 items at 721x1440 364 -> 150 us; what bounds it are the two barriers of
+// a block of rows and the LDS latency between them, as in the recurrence form.
 //
 // P̄_l^m is generated by the float64 three-term recurrence (as in the VALU
 // kernels) and contracted on matrix cores against all the items of a column
@@ -1976,6 +1993,8 @@ typedef short rm_short4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ unsigned rm_bf16(float v) {
   return (unsigned)__builtin_bit_cast(unsigned short, (__bf16)v);
 }
+
+enum { RM_RECUR = 0, RM_TABLE = 1 };  // where the kernel's P̄ comes from
 
 template <int OP>
 struct RmTraits;
@@ -2081,19 +2100,6 @@ __device__ __forceinline__ float rm_f32(double x) {
   return f;
 }
 
-// 4 x 4 exchange of lane groups: afterwards register t holds, in lane group g,
-// what lane group t held in register g (lane groups = 16-lane rows).
-__device__ __forceinline__ void lanegroup_transpose4(unsigned& r0, unsigned& r1, unsigned& r2, unsigned& r3) {
-  auto a = __builtin_amdgcn_permlane32_swap(r0, r2, false, false);
-  auto b = __builtin_amdgcn_permlane32_swap(r1, r3, false, false);
-  auto c = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
-  auto d = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
-  r0 = c[0];
-  r1 = c[1];
-  r2 = d[0];
-  r3 = d[1];
-}
-
 // LDS layout of legendre_rmma_kernel (bytes), shared with the host.
 struct RmLayout {
   int nb, ncol, pld, bld;
@@ -2125,8 +2131,8 @@ __host__ __device__ inline RmLayout rm_layout(int L, int h, int nt, int nw, int 
 
 // Split bfloat16 with 8 items per group is held to three waves per SIMD (at
 // most 168 registers); the other forms reach it or exceed it by design.
-template <typename T, int OP, int NT>
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu((OP == RM_BF16X3 && NT == 1) ? 3 : 1)))
+template <typename T, int OP, int NT, int SRC, int MODE, int WPE>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(WPE)))
 legendre_rmma_kernel(LegArgs<T> A) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   using TR = RmTraits<OP>;
@@ -2144,7 +2150,8 @@ legendre_rmma_kernel(LegArgs<T> A) {
   const int nr = L - m;
   const int nblk = (nr + 31) / 32;
   const int c0 = (lin - m * gridDim.y) * Q.ncol;
-  const int ncol = 2 * A.nb;
+  constexpr int mode = MODE;
+  static_assert(MODE == 0 || SRC == RM_TABLE, "the transforms alone: table form");
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, lg = lane >> 4;
@@ -2160,8 +2167,32 @@ legendre_rmma_kernel(LegArgs<T> A) {
   // 2 L h complex spectral entries: this chunk's spectra start here
   const float4* spc = reinterpret_cast<const float4*>(A.spec + A.soff0) + (size_t)(c0 / 2) * L * h + (size_t)m * h;
   const int j = 64 * wave + lane;
-  const double xj = A.xs[min(j, h - 1)];
-  const double sd = A.rseed[(size_t)m * h + min(j, h - 1)];
+  const double xj = SRC == RM_TABLE ? 0.0 : A.xs[min(j, h - 1)];
+  const double sd = SRC == RM_TABLE ? 0.0 : A.rseed[(size_t)m * h + min(j, h - 1)];
+  // table: this lane's column of the order's rows (hpad entries each, zero
+  // beyond h), the next block's values loaded while this one is contracted
+  const float* tabp = static_cast<const float*>(A.tab) + (size_t)toff * A.hpad + min(j, A.hpad - 1);
+  float vn[32], bn[2][4];
+  auto load_rows = [&](int r0) {
+#pragma unroll
+    for (int q = 0; q < 32; ++q) vn[q] = tabp[(size_t)min(r0 + q, nr - 1) * A.hpad];
+  };
+  if constexpr (SRC == RM_TABLE) load_rows(0);
+  // synthesis alone: this lane's operands straight from the coefficients (its
+  // item's component; rows 4 s + lane group of each parity), no barriers
+  const T* cin = nullptr;
+  if (mode == 2 && (li >> 1) < nit)
+    cin = reinterpret_cast<const T*>(A.coeff + A.items[A.item0 + c0 / 2 + (li >> 1)].coff + toff) + (li & 1);
+  auto load_coeff = [&](int r0) {
+#pragma unroll
+    for (int par = 0; par < 2; ++par)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const int r = r0 + 2 * (4 * s + lg) + par;
+        bn[par][s] = cin && r < nr ? (float)cin[2 * r] : 0.f;
+      }
+  };
+  if constexpr (mode == 2) load_coeff(0);
 
   // This wave's latitudes of the items' folded spectra, the analysis B
   // operands, loaded straight into registers (k = latitude 64 wave + KS s + the
@@ -2185,10 +2216,10 @@ legendre_rmma_kernel(LegArgs<T> A) {
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
       const int jj = pair_lat(g, odd ? 1 : 0);
-      fl[t][g] = il < nit && jj < h ? spc[(size_t)il * L * h + jj] : make_float4(0.f, 0.f, 0.f, 0.f);
+      fl[t][g] = il < nit && jj < h && mode != 2 ? spc[(size_t)il * L * h + jj] : make_float4(0.f, 0.f, 0.f, 0.f);
     }
   }
-  {
+  if constexpr (SRC != RM_TABLE) {
     double cv[2];
 #pragma unroll
     for (int u = 0; u < 2; ++u) cv[u] = A.rcoef[toff + min(tid + u * (int)blockDim.x, nr - 1)];
@@ -2231,6 +2262,10 @@ legendre_rmma_kernel(LegArgs<T> A) {
   // sensitive (gradient of 8 pairs at 360x720, worst of 6 inputs: error against
   // float64 2.0e-5 with f_00 from the float32 products).
   double* zs = reinterpret_cast<double*>(smem_raw + Q.o_z);
+  // a float32 table holds P̄_0^0 rounded: f_00 takes the exact value, and b_00 the
+  // ratio of the two, so that the rounding leaves the operator's constant mode
+  constexpr double P00 = 0.28209479177387814347;
+  constexpr double p00fix = P00 / (double)(float)P00;
   if constexpr (OP == RM_F32) {
     if (m == 0) {
 #pragma unroll
@@ -2263,14 +2298,29 @@ legendre_rmma_kernel(LegArgs<T> A) {
     // gamma and h_l of this block's rows, loaded now, stored to LDS before the
     // barrier, used by the combine after it
     const int gr = min(r0 + (tid & 31), nr - 1);
-    const double gld = A.rgam[toff + gr];
+    const double gld = SRC == RM_TABLE ? 1.0 : A.rgam[toff + gr];
     float hld[2];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const int e = min(tid + u * (int)blockDim.x, 8 * NT * 32 - 1), i = min(e >> 5, nit - 1);
-      hld[u] = A.hl[(size_t)(A.item0 + c0 / 2 + i) * A.hl_stride + m + min(r0 + (e & 31), nr - 1)];
+      hld[u] = mode != 0 ? 1.f
+                         : A.hl[(size_t)(A.item0 + c0 / 2 + i) * A.hl_stride + m + min(r0 + (e & 31), nr - 1)];
     }
-    float v[32];
+    float v[32], bcur[2][4];
+    if constexpr (SRC == RM_TABLE) {
+#pragma unroll
+      for (int q = 0; q < 32; ++q) {
+        v[q] = j < h ? vn[q] : 0.f;
+        if (mode != 2) TR::put(Pt, Q.pplane, (size_t)q * Q.pld + lane, v[q]);
+      }
+      if (blk + 1 < nblk) load_rows(r0 + 32);
+      if constexpr (mode == 2) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) bcur[e >> 2][e & 3] = bn[e >> 2][e & 3];
+        if (m == 0 && r0 == 0 && lg == 0) bcur[0][0] = (float)((double)bcur[0][0] * p00fix);
+        if (blk + 1 < nblk) load_coeff(r0 + 32);
+      }
+    } else
 #pragma unroll
     for (int hq = 0; hq < 32; hq += RQ) {  // coefficients in batches of RQ (registers)
       double cq[RQ];
@@ -2319,6 +2369,7 @@ legendre_rmma_kernel(LegArgs<T> A) {
     for (int par = 0; par < 2; ++par)
 #pragma unroll
       for (int t = 0; t < NT; ++t) acc[par][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    if (mode != 2)
 #pragma unroll
     for (int s = 0; s < NKS; ++s) {
 #pragma unroll
@@ -2331,6 +2382,7 @@ legendre_rmma_kernel(LegArgs<T> A) {
         for (int t = 0; t < NT; ++t) acc[par][t] = TR::mma(a, yb[s][par][t], acc[par][t]);
       }
     }
+    if constexpr (mode != 2) {
     // the combine's scale gamma^2 h_l per (parity, item, row of the parity);
     // zero past the order's end and past the chunk's items (blockDim is a
     // multiple of 32, so e & 31 is this thread's gamma row)
@@ -2345,8 +2397,8 @@ legendre_rmma_kernel(LegArgs<T> A) {
     for (int e = tid + 2 * blockDim.x; e < 8 * NT * 32; e += blockDim.x) {  // one-wave workgroups of 16 items
       const int i = e >> 5, rr = e & 31, r = r0 + rr;
       const bool ok = r < nr && i < nit;
-      const double g = ok ? A.rgam[toff + r] : 0.0;
-      const float hv = ok ? (float)A.hl[(size_t)(A.item0 + c0 / 2 + i) * A.hl_stride + m + r] : 0.f;
+      const double g = ok ? (SRC == RM_TABLE ? 1.0 : A.rgam[toff + r]) : 0.0;
+      const float hv = ok && mode != 0 ? 1.f : ok ? (float)A.hl[(size_t)(A.item0 + c0 / 2 + i) * A.hl_stride + m + r] : 0.f;
       scd[((rr & 1) * 8 * NT + i) * 16 + (rr >> 1)] = g * g * (double)hv;
     }
     // wave partials, [wave][parity][column][row of the parity] (rows padded to 20)
@@ -2364,6 +2416,9 @@ legendre_rmma_kernel(LegArgs<T> A) {
       constexpr int NC = 16 * NT;
       const int pn = idx >> 2, q4 = idx & 3;
       const int par = pn >= NC ? 1 : 0, n = pn - par * NC;
+      T* cp = nullptr;  // analysis alone: this column's coefficients
+      if (SRC == RM_TABLE && mode == 1 && (n >> 1) < nit)
+        cp = reinterpret_cast<T*>(A.coeff + A.items[A.item0 + c0 / 2 + (n >> 1)].coff + toff) + (n & 1);
       const f32x4_t* dp = reinterpret_cast<const f32x4_t*>(Dp) + (par * NC + n) * 5 + q4;
       f32x4_t sum = f32x4_t{0.f, 0.f, 0.f, 0.f};
       for (int w = 0; w < nw; ++w) sum += dp[w * 2 * NC * 5];
@@ -2374,11 +2429,21 @@ legendre_rmma_kernel(LegArgs<T> A) {
       if (OP == RM_F32 && m == 0 && r0 == 0 && par == 0 && q4 == 0) {
         double z = 0.0;
         for (int w = 0; w < nw; ++w) z += zs[w * NC + n];
-        o[0] = (float)(z * A.rseed[0] * sc[0]);
+        o[0] = SRC == RM_TABLE ? (float)(z * P00 * sc[0] * (mode == 0 ? p00fix : 1.0)) : (float)(z * A.rseed[0] * sc[0]);
+      }
+      if (SRC == RM_TABLE && mode == 1) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int r = r0 + 2 * (4 * q4 + e) + par;
+          if (cp && r < nr) cp[2 * r] = (T)o[e];
+        }
+        continue;
       }
       TR::put4(Bs, Q.bplane, (size_t)(par * NC + n) * Q.bld + 4 * q4, o);
     }
     __syncthreads();
+    }
+    if (SRC == RM_TABLE && mode == 1) continue;
     // the block's synthesis term
 #pragma unroll
     for (int par = 0; par < 2; ++par) {
@@ -2392,7 +2457,8 @@ legendre_rmma_kernel(LegArgs<T> A) {
           lanegroup_transpose4(a[0], a[1], a[2], a[3]);
 #pragma unroll
           for (int t = 0; t < NT; ++t) {
-            const Op b = TR::get(Bs, Q.bplane, ((size_t)par * Q.ncol + 16 * t + li) * Q.bld + 4 * s + lg);
+            const Op b = mode == 2 ? Op{bcur[par][s]}
+                                   : TR::get(Bs, Q.bplane, ((size_t)par * Q.ncol + 16 * t + li) * Q.bld + 4 * s + lg);
 #pragma unroll
             for (int jt = 0; jt < 4; ++jt) G[par][jt][t] = TR::mma(Op{__uint_as_float(a[jt])}, b, G[par][jt][t]);
           }
@@ -2426,6 +2492,7 @@ legendre_rmma_kernel(LegArgs<T> A) {
       }
     }
   }
+  if (SRC == RM_TABLE && mode == 1) return;
   // ---- the order's folded spectrum: G[j][n] (j = 64 wave + 16 jt + 4 lg + e)
   // stored straight from the accumulators: the two lanes of an item (its real
   // and imaginary column) trade halves so that each writes whole (E, O)
@@ -2817,29 +2884,52 @@ static hipError_t launch_mma_nt(const LegArgs<T>& a, hipStream_t stream) {
 
 template <typename T, typename TT>
 static hipError_t launch_mma_tt(const LegArgs<T>& a, int nt, hipStream_t stream) {
-  switch (nt) {
-    case 1:  // one item: its two columns only
-      return a.nb == 1 ? launch_mma_nt<T, TT, 1, true>(a, stream) : launch_mma_nt<T, TT, 1, false>(a, stream);
-    case 2: return launch_mma_nt<T, TT, 2, false>(a, stream);
-    default: return launch_mma_nt<T, TT, 4, false>(a, stream);
+  if constexpr (sizeof(TT) == 2) {
+    if (nt == 2) return launch_mma_nt<T, TT, 2, false>(a, stream);
+    if (nt > 2) return launch_mma_nt<T, TT, 4, false>(a, stream);
   }
+  // (float tables come here beyond 512 latitude pairs only, where one tile fits the LDS)
+  return a.nb == 1 ? launch_mma_nt<T, TT, 1, true>(a, stream)  // one item: its two columns only
+                   : launch_mma_nt<T, TT, 1, false>(a, stream);
+}
+
+template <typename T, int OP, int NT, int SRC, int MODE = 0, int WPE = (OP == RM_BF16X3 && NT == 1) ? 3 : 1>
+static hipError_t launch_rmma_nt(const LegArgs<T>& a, hipStream_t stream);
+
+template <typename T, typename TT, int MODE>
+static hipError_t launch_gemv(const LegArgs<T>& a, hipStream_t stream) {
+  SHOT_LAUNCH((legendre_gemv_kernel<T, TT, gemv_waves(), gemv_rows(), MODE>), dim3(a.L), dim3(64 * gemv_waves()),
+              gemv_lds_bytes(), stream, a);
+  return hipGetLastError();
 }
 
 template <typename T>
 hipError_t launch_legendre_mma(const LegArgs<T>& a, int table_kind, int nt, hipStream_t stream) {
   if (a.hpad % 32) return hipErrorInvalidValue;
-  if (a.nb == 1 && a.mode == 0 && a.hpad <= 512) {  // one item: the vector-unit kernel
-    const size_t lds = gemv_lds_bytes();
-    if (table_kind == TAB_BF16)
-      SHOT_LAUNCH((legendre_gemv_kernel<T, unsigned short, gemv_waves(), gemv_rows()>), dim3(a.L),
-                  dim3(64 * gemv_waves()), lds, stream, a);
-    else if (table_kind == TAB_F32)
-      SHOT_LAUNCH((legendre_gemv_kernel<T, float, gemv_waves(), gemv_rows()>), dim3(a.L), dim3(64 * gemv_waves()),
-                  lds, stream, a);
-    else
-      return hipErrorInvalidValue;
-    return hipGetLastError();
+  if (a.nb == 1 && a.hpad <= 512) {  // one item: the vector-unit kernel
+    if (table_kind == TAB_BF16 && a.mode == 0) return launch_gemv<T, unsigned short, 0>(a, stream);
+    if (table_kind == TAB_F32) {
+      switch (a.mode) {
+        case 0: return launch_gemv<T, float, 0>(a, stream);
+        case 1: return launch_gemv<T, float, 1>(a, stream);
+        default: return launch_gemv<T, float, 2>(a, stream);
+      }
+    }
   }
+  // float32 tables of at most 512 latitude pairs: the single-pass kernel
+  if constexpr (sizeof(T) == 4)
+    if (table_kind == TAB_F32 && a.h <= 512 && rmma_lds_bytes(a.L, a.h, 1, RM_F32) <= 160 * 1024)
+      switch (a.mode) {
+        case 0:
+          // 176 registers leave two waves per SIMD; holding them to 168 (four spilled)
+          // pays where the launch has waves for three (360x720: 48 items 124 -> 99
+          // us, 16 items 49 -> 55 us)
+          if ((long long)a.L * ((a.nb + 7) / 8) * ((a.h + 63) / 64) > 3072)
+            return launch_rmma_nt<T, RM_F32, 1, RM_TABLE, 0, 3>(a, stream);
+          return launch_rmma_nt<T, RM_F32, 1, RM_TABLE, 0, 2>(a, stream);
+        case 1: return launch_rmma_nt<T, RM_F32, 1, RM_TABLE, 1>(a, stream);
+        default: return launch_rmma_nt<T, RM_F32, 1, RM_TABLE, 2>(a, stream);
+      }
   if (table_kind == TAB_BF16) return launch_mma_tt<T, unsigned short>(a, nt, stream);
   if (table_kind == TAB_F32) return launch_mma_tt<T, float>(a, nt, stream);
   return hipErrorInvalidValue;
@@ -2848,7 +2938,7 @@ template hipError_t launch_legendre_mma<float>(const LegArgs<float>&, int, int, 
 template hipError_t launch_legendre_mma<double>(const LegArgs<double>&, int, int, hipStream_t);
 
 // Recurrence-fed matrix-core kernel: float32 fields only; waves = ceil(h/64) <= 8.
-template <typename T, int OP, int NT>
+template <typename T, int OP, int NT, int SRC, int MODE, int WPE>
 static hipError_t launch_rmma_nt(const LegArgs<T>& a, hipStream_t stream) {
   if constexpr (sizeof(T) != 4) {
     return hipErrorInvalidValue;
@@ -2860,14 +2950,14 @@ static hipError_t launch_rmma_nt(const LegArgs<T>& a, hipStream_t stream) {
     if (Q.total > 65536) {
       static size_t attr_bytes = 65536;  // dynamic LDS enabled so far for this instantiation
       if (Q.total > attr_bytes) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&legendre_rmma_kernel<T, OP, NT>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&legendre_rmma_kernel<T, OP, NT, SRC, MODE, WPE>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)Q.total);
         if (e != hipSuccess) return e;
         attr_bytes = Q.total;
       }
     }
     dim3 grid(a.L, (2 * a.nb + Q.ncol - 1) / Q.ncol);
-    SHOT_LAUNCH((legendre_rmma_kernel<T, OP, NT>), grid, dim3(64 * nw), Q.total, stream, a);
+    SHOT_LAUNCH((legendre_rmma_kernel<T, OP, NT, SRC, MODE, WPE>), grid, dim3(64 * nw), Q.total, stream, a);
     return hipGetLastError();
   }
 }
@@ -2875,8 +2965,8 @@ static hipError_t launch_rmma_nt(const LegArgs<T>& a, hipStream_t stream) {
 template <typename T, int OP>
 static hipError_t launch_rmma_op(const LegArgs<T>& a, int nt, hipStream_t stream) {
   switch (nt) {
-    case 1: return launch_rmma_nt<T, OP, 1>(a, stream);
-    case 2: return launch_rmma_nt<T, OP, 2>(a, stream);
+    case 1: return launch_rmma_nt<T, OP, 1, RM_RECUR>(a, stream);
+    case 2: return launch_rmma_nt<T, OP, 2, RM_RECUR>(a, stream);
     default: return hipErrorInvalidValue;
   }
 }
