@@ -288,7 +288,7 @@ class Plan:
             unit = self.field_size(0) if per_item == "field" else 2 * self.ncoeff(0)
             if x.numel() % unit:
                 raise ValueError("tensor size is not a multiple of the item size")
-            grid_of_item = [0] * (x.numel() // unit)
+            return [0] * (x.numel() // unit)
         grid_of_item = [int(g) for g in grid_of_item]
         unit = [self.field_size(g) if per_item == "field" else 2 * self.ncoeff(g) for g in grid_of_item]
         if sum(unit) != x.numel():

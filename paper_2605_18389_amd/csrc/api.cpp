@@ -633,50 +633,90 @@ shot_status carve(shot_plan_s* P, const Layout& Lo, int nitems, bool sinkhorn, i
   return SHOT_OK;
 }
 
-// Per-call status arrays: no breakdown yet, kernel ratio +inf.
+// The item descriptor of sorted position si (soff: its spectral offset).
 template <typename T>
-shot_status init_status(Work<T>& W, int nitems, hipStream_t s) {
-  std::vector<int> brk0(nitems, INT_MAX);
-  std::vector<double> kr0(nitems, INFINITY);
-  HIP_TRY(hipMemcpyAsync(W.brk, brk0.data(), sizeof(int) * nitems, hipMemcpyHostToDevice, s));
-  HIP_TRY(hipMemcpyAsync(W.kr, kr0.data(), sizeof(double) * nitems, hipMemcpyHostToDevice, s));
-  HIP_TRY(hipStreamSynchronize(s));
+ItemDev item_desc(const Layout& Lo, int si, int64_t soff, const std::vector<double>& eps,
+                  const std::vector<double>& tau, const std::vector<const void*>& pp,
+                  const std::vector<const void*>& qq) {
+  const int ui = Lo.order[si];
+  ItemDev I;
+  I.foff = Lo.user_foff[ui];
+  I.soff = soff;
+  I.coff = Lo.user_coff[ui];
+  // kernels index p and q with the item's field offset: pre-subtract it, so
+  // that an item's marginals may live anywhere (the divergence aliases them)
+  I.p = pp.empty() ? nullptr : static_cast<const T*>(pp[ui]) - I.foff;
+  I.q = qq.empty() ? nullptr : static_cast<const T*>(qq[ui]) - I.foff;
+  I.eps = eps.empty() ? 0.0 : eps[ui];
+  I.tau = tau.empty() ? INFINITY : tau[ui];
+  I.balanced = std::isinf(I.tau) ? 1 : 0;
+  I.lam = I.balanced ? 1.0 : I.tau / (I.tau + I.eps);
+  I.eot = I.balanced ? 0.0 : I.eps / I.tau;
+  I.pad = 0;
+  return I;
+}
+
+// Descriptors and heat multipliers through the arguments of setup launches of N items.
+template <typename T, int N>
+shot_status setup_items(shot_plan_s* P, const Layout& Lo, const int32_t* goi, const std::vector<double>& eps,
+                        const std::vector<double>& tau, const std::vector<double>& tvals,
+                        const std::vector<const void*>& pp, const std::vector<const void*>& qq, Work<T>& W,
+                        hipStream_t s) {
+  const int nitems = (int)Lo.order.size();
+  static_assert(sizeof(SetupArgs<T, N>) <= 4096, "kernel arguments");
+  SetupArgs<T, N> a{};
+  a.items = W.items;
+  a.hl = W.hl;
+  a.brk = W.brk;
+  a.kr = W.kr;
+  a.Lmax = Lo.Lmax;
+  for (int first = 0; first < nitems; first += N) {
+    a.first = first;
+    a.count = std::min(N, nitems - first);
+    for (int i = 0; i < a.count; ++i) {
+      const int si = first + i, ui = Lo.order[si];
+      a.L[i] = P->grids[goi[ui]].d.L;
+      a.t[i] = tvals[ui];
+      a.it[i] = item_desc<T>(Lo, si, Lo.sorted_soff[si], eps, tau, pp, qq);
+    }
+    HIP_TRY((launch_setup<T, N>(a, s)));
+  }
   return SHOT_OK;
 }
 
-// Host-side item descriptors and heat multipliers (sorted order).
+// Item descriptors, heat multipliers and (Sinkhorn workspaces) status words of
+// a call, in sorted order, enqueued on the stream: up to 96 items travel in
+// launch arguments, 32 a launch (2 for the smallest calls); larger calls, whose
+// run time dwarfs it, copy from host memory and wait for the copies.
 template <typename T>
 shot_status upload_items(shot_plan_s* P, const Layout& Lo, const int32_t* grid_of_item,
                          const std::vector<double>& eps, const std::vector<double>& tau,
                          const std::vector<double>& tvals, const std::vector<const void*>& pp,
                          const std::vector<const void*>& qq, Work<T>& W, hipStream_t s) {
   const int nitems = (int)Lo.order.size();
+  // a call cannot be captured: its workspace belongs to the plan, not to a graph
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  HIP_TRY(hipStreamIsCapturing(s, &cap));
+  if (cap != hipStreamCaptureStatusNone) return hip_fail(hipErrorStreamCaptureUnsupported, "call under capture", __LINE__);
+  if (nitems <= 2) return setup_items<T, 2>(P, Lo, grid_of_item, eps, tau, tvals, pp, qq, W, s);
+  if (nitems <= 96) return setup_items<T, 32>(P, Lo, grid_of_item, eps, tau, tvals, pp, qq, W, s);
   std::vector<ItemDev> items(nitems);
   std::vector<T> hl((size_t)nitems * Lo.Lmax, (T)0);
-  int64_t soff = 0;
   for (int si = 0; si < nitems; ++si) {
     const int ui = Lo.order[si];
-    const GridRec& g = P->grids[grid_of_item[ui]];
-    ItemDev& I = items[si];
-    I.foff = Lo.user_foff[ui];
-    I.soff = soff;
-    I.coff = Lo.user_coff[ui];
-    soff += 2LL * g.d.L * g.h;
-    // kernels index p and q with the item's field offset: pre-subtract it, so
-    // that an item's marginals may live anywhere (the divergence aliases them)
-    I.p = pp.empty() ? nullptr : static_cast<const T*>(pp[ui]) - I.foff;
-    I.q = qq.empty() ? nullptr : static_cast<const T*>(qq[ui]) - I.foff;
-    I.eps = eps.empty() ? 0.0 : eps[ui];
-    I.tau = tau.empty() ? INFINITY : tau[ui];
-    I.balanced = std::isinf(I.tau) ? 1 : 0;
-    I.lam = I.balanced ? 1.0 : I.tau / (I.tau + I.eps);
-    I.eot = I.balanced ? 0.0 : I.eps / I.tau;
-    I.pad = 0;
+    items[si] = item_desc<T>(Lo, si, Lo.sorted_soff[si], eps, tau, pp, qq);
     const double t = tvals[ui];
-    for (int l = 0; l < g.d.L; ++l) hl[(size_t)si * Lo.Lmax + l] = (T)std::exp(-t * l * (l + 1.0));
+    for (int l = 0; l < P->grids[grid_of_item[ui]].d.L; ++l)
+      hl[(size_t)si * Lo.Lmax + l] = (T)std::exp(-t * l * (l + 1.0));
   }
   HIP_TRY(hipMemcpyAsync(W.items, items.data(), sizeof(ItemDev) * nitems, hipMemcpyHostToDevice, s));
   HIP_TRY(hipMemcpyAsync(W.hl, hl.data(), sizeof(T) * hl.size(), hipMemcpyHostToDevice, s));
+  std::vector<int> brk0(nitems, INT_MAX);
+  std::vector<double> kr0(nitems, INFINITY);
+  if (W.brk) {
+    HIP_TRY(hipMemcpyAsync(W.brk, brk0.data(), sizeof(int) * nitems, hipMemcpyHostToDevice, s));
+    HIP_TRY(hipMemcpyAsync(W.kr, kr0.data(), sizeof(double) * nitems, hipMemcpyHostToDevice, s));
+  }
   HIP_TRY(hipStreamSynchronize(s));  // host staging vectors go out of scope
   return SHOT_OK;
 }
@@ -1027,7 +1067,6 @@ shot_status solve_impl(shot_plan_s* P, const SolveSpec& S, T* phi, T* psi, shot_
     tv[i] = S.prm[i].eps / 4.0;  // t = eps/4 (Alg. 1)
   }
   ST_TRY(upload_items<T>(P, Lo, S.grid.data(), eps, tau, tv, S.p, S.q, W, s));
-  ST_TRY(init_status(W, nitems, s));
 
   auto each_group = [&](auto&& fn) -> shot_status {
     for (const Group& G : Lo.groups) {
@@ -1446,7 +1485,6 @@ shot_status adjoint_impl(shot_plan_s* P, const SolveSpec& S, int CK, T** pbar_ou
     tv[i] = S.prm[i].eps / 4.0;
   }
   ST_TRY(upload_items<T>(P, Lo, S.grid.data(), eps, tau, tv, S.p, S.q, W, s));
-  ST_TRY(init_status(W, nitems, s));
   // gradient arena
   const size_t F = (size_t)Lo.field_total;
   size_t off = 0;

@@ -2659,8 +2659,42 @@ __global__ void __launch_bounds__(256) combine_kernel(const CombineDev* __restri
 }
 
 // ---------------------------------------------------------------------------
+// Per-call data of up to N items from the launch's arguments: descriptors, heat
+// multipliers h_l = exp(-t l(l+1)) (zero past an item's band limit), status
+// words.  grid = (blocks over Lmax, items).  Two copies from pageable host memory
+// and the wait for them, which this replaces, kept the host from queueing a call
+// while the one before it ran (2 float64 items at 193x400, synthesis: 29 us a
+// call, 15 of them on the GPU).
+// ---------------------------------------------------------------------------
+template <typename T, int N>
+__global__ void __launch_bounds__(256) setup_kernel(SetupArgs<T, N> A) {
+  const int i = blockIdx.y, l = blockIdx.x * 256 + threadIdx.x;
+  const size_t at = (size_t)A.first + i;
+  if (l < A.Lmax) A.hl[at * A.Lmax + l] = l < A.L[i] ? (T)exp(-A.t[i] * l * (l + 1.0)) : (T)0;
+  if (blockIdx.x == 0) {
+    constexpr int W = sizeof(ItemDev) / 4;
+    if (threadIdx.x < W)
+      reinterpret_cast<int*>(A.items + at)[threadIdx.x] = reinterpret_cast<const int*>(&A.it[i])[threadIdx.x];
+    if (A.brk && threadIdx.x == 0) {
+      A.brk[at] = INT_MAX;
+      A.kr[at] = INFINITY;
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
+template <typename T, int N>
+hipError_t launch_setup(const SetupArgs<T, N>& a, hipStream_t stream) {
+  hipLaunchKernelGGL((setup_kernel<T, N>), dim3((a.Lmax + 255) / 256, a.count), dim3(256), 0, stream, a);
+  return hipGetLastError();
+}
+template hipError_t launch_setup<float, 2>(const SetupArgs<float, 2>&, hipStream_t);
+template hipError_t launch_setup<float, 32>(const SetupArgs<float, 32>&, hipStream_t);
+template hipError_t launch_setup<double, 2>(const SetupArgs<double, 2>&, hipStream_t);
+template hipError_t launch_setup<double, 32>(const SetupArgs<double, 32>&, hipStream_t);
+
 // Optional start/stop events of the next row or Legendre launch: the events
 // are attached to the dispatch itself (hipExtLaunchKernelGGL), so they time
 // the kernel's execution rather than the gap before it.

@@ -172,6 +172,22 @@ struct LegArgs {
                           // consecutive, 2 L h complex entries each)
 };
 
+// Per-call data of `count` items from item `first` on, passed in a launch's
+// arguments (at most 4 KiB); brk, kr: status words to reset (nullptr: none).
+template <typename T, int N>
+struct SetupArgs {
+  ItemDev* items;
+  T* hl;
+  int* brk;
+  double* kr;
+  int first, count, Lmax;
+  int L[N];
+  double t[N];
+  ItemDev it[N];
+};
+template <typename T, int N>
+hipError_t launch_setup(const SetupArgs<T, N>& a, hipStream_t stream);
+
 // Launchers (kernels.hip).  All enqueue on `stream` and return the launch status.
 // set_launch_events: time the next row/Legendre launch with these events.
 void set_launch_events(hipEvent_t start, hipEvent_t stop);
