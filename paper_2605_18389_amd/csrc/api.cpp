@@ -894,6 +894,21 @@ bool use_t64(const GridRec& g) {
   return g.tab_kind == TAB_F64 && g.d_tab != nullptr && g.tune_jpt == 0 && g.tune_ib == 0 && t64_fits(g.h);
 }
 
+// Recurrence-fed float64 matrix-core kernel (8 items per workgroup) instead of
+// the row-split kernel, where no tuning asks for one: from three row-split item
+// chunks per chunk of 8 on, and from 1024 row-split workgroups on (they are
+// resident 768 at a time).  Heat apply of float32 plans, row-split -> this, us:
+// below the line 8 items at 128x256 9.8 -> 10.1, 4 at 256x512 17.4 -> 21.5, 8 at
+// 180x360 15.3 -> 16.2, 10 at 360x720 65 -> 72; above it 16 at 128x256 13.0 ->
+// 12.2, 7 at 256x512 28.8 -> 21.2, 12 and 16 at 180x360 18.6 -> 19.1 and 26.5 ->
+// 19.1, 5 at 360x720 44.7 -> 40.1; float64 plans gain more on both sides.
+bool use_r64(const shot_plan_s* P, const GridRec& g, int nb, int leg_mode) {
+  if (g.tab_kind != TAB_RECUR || g.tune_ib != 0 || g.tune_jpt != 0 || !r64_fits(g.d.L, g.h)) return false;
+  if (rmma_tiles(P, g, nb, leg_mode, nullptr) > 0) return false;
+  const int ib = split_ib(P, g, nb), chunks = (nb + ib - 1) / ib;
+  return chunks >= 3 * ((nb + 7) / 8) && g.d.L * chunks >= 1024;
+}
+
 template <typename T>
 shot_status run_rows(shot_plan_s* P, const RowArgs<T>& a, int nb, hipStream_t s) {
   ProfScope ps(P, s, 1);
@@ -905,6 +920,7 @@ shot_status run_rows(shot_plan_s* P, const RowArgs<T>& a, int nb, hipStream_t s)
 // kernel runs it) and its items per workgroup.
 const SplitSched* leg_split(const shot_plan_s* P, const GridRec& g, int nb, int leg_mode, int* ib_out) {
   if (mma_tiles(P, g, nb) > 0 || rmma_tiles(P, g, nb, leg_mode, nullptr) > 0 || !use_split(P, g)) return nullptr;
+  if (use_r64(P, g, nb, leg_mode)) return nullptr;
   const int ib = split_ib(P, g, nb);
   if (ib_out) *ib_out = ib;
   return pick_sched(P, g, nb, ib);
@@ -925,6 +941,8 @@ shot_status run_leg(shot_plan_s* P, const GridRec& g, LegArgs<T> a, hipStream_t 
     }
   }
   if (done) {
+  } else if (use_r64(P, g, a.nb, a.mode)) {
+    e = launch_legendre_r64<T>(a, s);
   } else if (nt > 0) {
     e = launch_legendre_mma<T>(a, g.tab_kind, nt, s);
   } else if (rnt > 0) {
@@ -1341,7 +1359,7 @@ shot_status autotune_impl(shot_plan_s* P, GridRec& g, const Layout& Lo, int nite
       cand.push_back({ib, -1});  // VALU table kernel
     }
   }
-  if (g.tab_kind == TAB_F64 && t64_fits(g.h)) cand.push_back({0, 0});  // matrix cores
+  if (g.tab_kind == TAB_RECUR || (g.tab_kind == TAB_F64 && t64_fits(g.h))) cand.push_back({0, 0});  // float64 matrix cores
   if (mma_table(g))
     for (int nt : {1, 2, 4})
       if (16 * nt <= 2 * std::max(nitems, 8)) cand.push_back({0, nt});
@@ -1369,10 +1387,12 @@ shot_status autotune_impl(shot_plan_s* P, GridRec& g, const Layout& Lo, int nite
       if (mma_tiles(P, g, nitems) != c.second) continue;  // does not fit LDS
     } else if (use_t64(g)) {
       // (fits: checked when the candidate was listed)
+    } else if (g.tab_kind == TAB_RECUR && c.first == 0) {
+      if (!use_r64(P, g, nitems, 0)) continue;
     } else if (use_split(P, g) ? split_ib(P, g, nitems) != c.first : pick_ib(P, g, nitems) != c.first) {
       continue;  // does not fit LDS
     }
-    if (g.tab_kind == TAB_RECUR && c.first < 8 && c.second == 0 && !use_split(P, g)) continue;
+    if (g.tab_kind == TAB_RECUR && c.first > 0 && c.first < 8 && c.second == 0 && !use_split(P, g)) continue;
     shot_status st = SHOT_OK;
     for (int w = 0; w < 2 && st == SHOT_OK; ++w) st = run_leg<T>(P, g, leg_args<T>(g, G, W, Lo.Lmax, Lo), s);
     if (st != SHOT_OK) continue;

@@ -220,6 +220,10 @@ size_t mma_lds_bytes(int L, int hpad, int nt, int table_kind, bool narrow = fals
 // Matrix-core kernel of float64 tables (legendre64.hip), at most 512 latitude pairs.
 bool t64_fits(int h);
 hipError_t launch_legendre_t64(const LegArgs<double>& a, hipStream_t stream);
+// Its recurrence-fed form.
+bool r64_fits(int L, int h);
+template <typename T>
+hipError_t launch_legendre_r64(const LegArgs<T>& a, hipStream_t stream);
 
 template <typename T>
 hipError_t launch_reduce(const RowArgs<T>& a, int nb, int nchk_done, double* res, double* ehist,
