@@ -21,7 +21,7 @@
 // Arithmetic, partial sums and their slots are those of row_kernel; a wave
 // writes its sums at its first pair and the neutral element at the others.
 // Measured per launch (before -> after): Sinkhorn half of 24 items at 360x720
-// 41 -> 32 us (75 MB, 2.4 TB/s), reverse half of 16 items 46 -> 33 us, heat
+// 41 -> 32 us (75 MB, 2.4 TB/s), reverse half of 16 items 46 -> 32 us, heat
 // apply rows of 16 items 21 + 28 -> 14 + 11 us; 24 HEALPix items at Nside 64
 // 56 -> 24 us, 4 at Nside 256 161 -> 65 us; one float64 item of 256-point rows
 // 12.8 -> 7.8 us.  What bounds it now: issue (about 3000 instructions per
@@ -306,10 +306,11 @@ __device__ __forceinline__ cpx<T>* rt_fft(cpx<T>* a, cpx<T>* b, int N, const int
 
 // ---------------------------------------------------------------- pointwise
 // What one column of a pair needs besides the transformed rows: two values of
-// its first and of its second input field.
+// its first and of its second input field, of the gradient field it adds to and
+// of v-bar.
 template <typename T>
 struct Col {
-  T a[2], b[2];
+  T a[2], b[2], g[2], w[2];
 };
 
 __device__ __forceinline__ bool positive_finite(float x) { return __builtin_amdgcn_classf(x, 0x100 | 0x80); }
@@ -395,18 +396,19 @@ __device__ __forceinline__ void point(const RowArgs<T>& A, const ItemDev& I, Pai
         const T u = C.b[rr], pv = C.a[rr];
         T ub = (T)S.s1 + kt;
         if (A.k == A.kT) ub += (T)I.eps * S.aj * pv / u;
-        if (S.act) A.gA[fidx] += ub * u / pv;
+        if (S.act) A.gA[fidx] = C.g[rr] + ub * u / pv;
         nv[rr] = -ub * u * u / pv;
       } else {
         const T v = C.b[rr], qv = C.a[rr];
         S.acc += (double)kt * (double)v;
-        if (S.act) A.gB[fidx] += S.gs * kt * v / qv;
+        if (S.act) A.gB[fidx] = C.g[rr] + S.gs * kt * v / qv;
         nv[rr] = -S.gs * kt * v * v / qv;
       }
     } else {
       const T kt = S.aj * zr;
       const T ea = (T)I.eps, lam = (T)I.lam, eta = (T)I.eot, tau = (T)I.tau;
       const bool last = (A.k == A.kT);
+      // u^(1/lam) = u^(1 + eps/tau) = u / u^(-eps/tau): one power a point
       if constexpr (KIND == RK_ADJU_V1) {
         const T v = C.b[rr];
         const T vb = kt;
@@ -416,17 +418,17 @@ __device__ __forceinline__ void point(const RowArgs<T>& A, const ItemDev& I, Pai
       } else if constexpr (KIND == RK_ADJU_B) {
         const T v = C.b[rr], qv = C.a[rr], sBb = (T)S.s2;
         const T pe = pow(v, -eta);
-        const T vhb = S.gs * A.vbar[fidx] - eta * sBb * S.aj * qv * (pe / v);
-        if (S.act) A.gB[fidx] += sBb * S.aj * pe + lam * vhb * v / qv;
-        nv[rr] = -lam * vhb * v * pow(v, (T)1 / lam) / qv;
+        const T vhb = S.gs * C.w[rr] - eta * sBb * S.aj * qv * (pe / v);
+        if (S.act) A.gB[fidx] = C.g[rr] + (sBb * S.aj * pe + lam * vhb * v / qv);
+        nv[rr] = -lam * vhb * v * (v / pe) / qv;
         (void)ea; (void)tau; (void)last;
       } else if constexpr (KIND == RK_ADJU_A) {
         const T u = C.b[rr], pv = C.a[rr], sAb = (T)S.s1;
         const T pe = pow(u, -eta);
         T uhb = kt - eta * sAb * S.aj * pv * (pe / u);
         if (last) uhb += ea * S.aj * pv * pow(u / S.gs, -eta - (T)1) / S.gs;
-        if (S.act) A.gA[fidx] += sAb * S.aj * pe + lam * uhb * u / pv;
-        nv[rr] = -lam * uhb * u * pow(u, (T)1 / lam) / pv;
+        if (S.act) A.gA[fidx] = C.g[rr] + (sAb * S.aj * pe + lam * uhb * u / pv);
+        nv[rr] = -lam * uhb * u * (u / pe) / pv;
         (void)tau;
       }
     }
@@ -438,7 +440,7 @@ template <typename T, int KIND>
 __device__ __forceinline__ Col<T> load_col(const RowArgs<T>& A, const ItemDev& I, const PairState<T>& S, long long c) {
   using GT = const __attribute__((address_space(1))) T;
   Col<T> C;
-  C.a[0] = C.a[1] = C.b[0] = C.b[1] = (T)0;
+  C.a[0] = C.a[1] = C.b[0] = C.b[1] = C.g[0] = C.g[1] = C.w[0] = C.w[1] = (T)0;
   const long long i1 = S.r1 + c, i2 = S.r2 + c;
   if constexpr (KIND == RK_SINK) {
     GT* F = (GT*)static_cast<const T*>(A.mode == ROW_SINK_U ? I.p : I.q);
@@ -458,6 +460,14 @@ __device__ __forceinline__ Col<T> load_col(const RowArgs<T>& A, const ItemDev& I
       GT* F = (GT*)static_cast<const T*>(uside ? I.p : I.q);
       C.a[0] = F[i1];
       C.a[1] = F[i2];
+      GT* D = (GT*)(uside ? A.gA : A.gB);
+      C.g[0] = D[i1];
+      C.g[1] = D[i2];
+    }
+    if constexpr (KIND == RK_ADJU_B) {
+      GT* V = (GT*)A.vbar;
+      C.w[0] = V[i1];
+      C.w[1] = V[i2];
     }
   }
   return C;
@@ -474,6 +484,8 @@ __device__ __forceinline__ Col<T> pick_col(const Col<T> (&col)[R], int e) {
     for (int q = 0; q < 2; ++q) {
       C.a[q] = e == r ? col[r].a[q] : C.a[q];
       C.b[q] = e == r ? col[r].b[q] : C.b[q];
+      C.g[q] = e == r ? col[r].g[q] : C.g[q];
+      C.w[q] = e == r ? col[r].w[q] : C.w[q];
     }
   return C;
 }
@@ -485,12 +497,22 @@ struct alignas(16) EO {
   cpx<T> e, o;
 };
 
+// Waves per SIMD a kernel's registers leave room for.  The adjoint kinds hold
+// more fields per column; one wave fewer keeps them out of scratch memory
+// (unbalanced reverse half of 16 HEALPix items at Nside 64: 26.2 -> 23.9 us).
+constexpr int row_waves(int real_bytes, int nc, int kind) {
+  if (real_bytes == 8) return 2;
+  if (nc == 720) return kind >= RK_ADJU_B ? 4 : 5;
+  if (nc == 0) return kind >= RK_ADJ ? 3 : 4;
+  return nc == 1024 && kind == RK_ADJU_A ? 3 : 4;
+}
+
 // ------------------------------------------------------------------- kernel
 // NC > 0: compile-time row length, NPC pairs per workgroup.  NC == 0: run-time
 // length or HEALPix rings, blockDim / TP pairs per workgroup; TP > 64: one
 // pair per workgroup, stages separated by workgroup barriers.
 template <typename T, int NC, int TP, int NPC, int KIND>
-__global__ void __launch_bounds__(NC > 0 ? TP * NPC : (TP > 64 ? TP : 256), sizeof(T) == 4 ? (NC == 720 ? 5 : 4) : 2)
+__global__ void __launch_bounds__(NC > 0 ? TP * NPC : (TP > 64 ? TP : 256), row_waves(sizeof(T), NC, KIND))
 row_wave_kernel(RowArgs<T> A) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   constexpr bool CT = NC > 0;
