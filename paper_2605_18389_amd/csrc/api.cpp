@@ -1631,10 +1631,14 @@ shot_status adjoint_impl(shot_plan_s* P, const SolveSpec& S, int CK, T** pbar_ou
         a.k = k;
         a.ubuf0 = a.ubuf1 = hu + F * slot;
         if (k == k0 + 1 && k0 > 0) a.gk = ckg + (size_t)(seg - 1) * nitems;
+        if (k > k0 + 1) {  // this half forms the gauge of k - 1: keep it
+          a.gstride = unbal ? 3 : 1;
+          a.gout = gh + (size_t)(slot - 1) * nitems * a.gstride;
+        }
         if (fwd_info && k - 1 >= 1 && (k - 1) % C == 0) a.chk_slot = (k - 1) / C - 1;
         return run_rows<T>(P, a, G.count, s);
       }));
-      if (!unbal)  // s_k = sum u-hat_k
+      if (!unbal && k == k1)  // s_k = sum u-hat_k
         for (const Group& G : Lo.groups) {
           RowArgs<T> a = base_args(G, P->grids[G.grid]);
           HIP_TRY(launch_gauge<T>(a, G.count, k, gh + (size_t)slot * nitems, s));
@@ -1648,7 +1652,7 @@ shot_status adjoint_impl(shot_plan_s* P, const SolveSpec& S, int CK, T** pbar_ou
         a.vbuf0 = a.vbuf1 = hv + F * slot;
         return run_rows<T>(P, a, G.count, s);
       }));
-      if (unbal)  // (g_k, S_A, S_B): needs both halves' partial sums
+      if (unbal && k == k1)  // (g_k, S_A, S_B): needs both halves' partial sums
         for (const Group& G : Lo.groups) {
           RowArgs<T> a = base_args(G, P->grids[G.grid]);
           HIP_TRY(launch_gauge3<T>(a, G.count, k, gh + (size_t)slot * nitems * 3, s));

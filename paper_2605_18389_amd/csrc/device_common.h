@@ -525,6 +525,19 @@ __device__ __forceinline__ T* ubuf_of(const RowArgs<T>& A, int k) { return (k & 
 template <typename T>
 __device__ __forceinline__ T* vbuf_of(const RowArgs<T>& A, int k) { return (k & 1) ? A.vbuf1 : A.vbuf0; }
 
+// What a U half that forms the previous iteration's gauge anyway keeps of it for
+// the reverse sweep (one thread per item; a launch of its own took 4.5 us).
+template <typename T>
+__device__ __forceinline__ void store_gauge(const RowArgs<T>& A, int it, double g, double s0, double s1) {
+  if (!A.gout) return;
+  double* o = A.gout + (size_t)A.gstride * it;
+  o[0] = g;
+  if (A.gstride == 3) {
+    o[1] = s0;
+    o[2] = s1;
+  }
+}
+
 // Gauge g_k: after iteration k the Alg. 1 scalings are u_k = u_hat/g_k and
 // v_k = g_k v_hat, with g_k = s = sum u_hat (balanced) or exp(-c/eps) with
 // c = tau/2 (log sum a p u_hat^(-eps/tau) - log sum a q v_hat^(-eps/tau)).
@@ -538,9 +551,9 @@ __device__ double gauge(const RowArgs<T>& A, const ItemDev& I, int it, int k, do
   }
   s0 = block_sum(s0, sh);
   s1 = block_sum(s1, sh);
-  if (I.balanced) return s0;
-  const double c = 0.5 * I.tau * (log(s0) - log(s1));
-  return exp(-c / I.eps);
+  const double g = I.balanced ? s0 : exp(-(0.5 * I.tau * (log(s0) - log(s1))) / I.eps);
+  if (A.mode == ROW_SINK_U && blockIdx.x == 0 && threadIdx.x == 0) store_gauge(A, it, g, s0, s1);
+  return g;
 }
 
 // Folded spectrum entry (E, O) of order m and row pair jp of item `it`: read

@@ -729,6 +729,7 @@ __global__ void __launch_bounds__(BS) row_sink_kernel(RowArgs<T> A) {
         s1 += shw[w][1];
       }
       g = I.balanced ? s0 : exp(-(0.5 * I.tau * (log(s0) - log(s1))) / I.eps);
+      if (blockIdx.x == 0 && tid == 0) store_gauge(A, it, g, s0, s1);
     }
   }
   const T gs = (T)g;

@@ -729,6 +729,7 @@ row_wave_kernel(RowArgs<T> A) {
           b += shw[w][1];
         }
         S.g = I.balanced ? a : exp(-(0.5 * I.tau * (log(a) - log(b))) / I.eps);
+        if (blockIdx.x == 0 && tid == 0) store_gauge(A, it, S.g, a, b);
       }
       S.gs = (T)S.g;
     }

@@ -113,6 +113,8 @@ struct RowArgs {
   T* gA;              // p-bar accumulator (layout of fields)
   T* gB;              // q-bar accumulator
   double* adjp;       // [nitems][hs] partial sums of s-bar
+  double* gout;       // SINK_U: where the gauge of iteration k-1 (gstride 3: with its two sums)
+  int gstride;        // goes, gstride entries per item; nullptr: nowhere
   const double* gk;   // [nitems] SINK_U: gauge of iteration k-1 to use instead of the partial sums;
                       // adjoint modes: s of the iteration whose u-hat / v-hat are read
   int kT;             // adjoint: last iteration T (its u-bar term enters ROW_ADJ_A)
