@@ -1234,6 +1234,15 @@ __global__ void __launch_bounds__(256) legendre_recur_kernel(LegArgs<T> A) {
 // several parts (so that long orders spread over several compute units) has
 // each part store its sum to a partial buffer; the consumer adds the parts in
 // part order, which keeps the result independent of timing.
+//
+// ONE: heat applies of few chains per lane in one pass.  A block's recurrence
+// values stay in registers until its analysis sums are reduced, and its
+// synthesis terms follow at once: the recurrence runs once (6 float64
+// operations a point instead of 8) and neither the checkpoints nor a barrier
+// stand between the passes.  Same operations in the same order, so the results
+// are bit for bit those of two passes.  One item, two passes -> one, us: 65
+// latitude pairs at L = 128 7.5 -> 6.1 (float64 7.2 -> 6.4), 90 at L = 180 8.5 ->
+// 7.2, 180 at L = 360 13.9 -> 12.6; 2 items, 32 pairs at L = 64 6.8 -> 5.3.
 // ---------------------------------------------------------------------------
 
 // A copy of a lane-varying index that the compiler cannot see through: the
@@ -1261,7 +1270,7 @@ __device__ __forceinline__ void prio_by_blocks(int left) {
 // Three waves per SIMD where the registers allow it without spilling: then
 // a launch of up to 3 x 256 workgroups is resident at once, and the host's
 // dispatch order balances the rows that meet on one compute unit.
-template <typename T, int IB, int C, int NV>
+template <typename T, int IB, int C, int NV, bool ONE>
 __global__ void __launch_bounds__(256, IB * C > 6 ? 2 : 3) legendre_split_kernel(LegArgs<T> A) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   using R = T;
@@ -1347,7 +1356,7 @@ __global__ void __launch_bounds__(256, IB * C > 6 ? 2 : 3) legendre_split_kernel
     for (int q = tid; q < npl; q += 256) bs[(size_t)i * maxpl + q] = make_double2(0.0, 0.0);
   // this order's folded spectrum, staged once per workgroup in the LDS that
   // the synthesis partial sums reuse later (read into registers before then)
-  if (A.mode != 2)
+  if (ONE || A.mode != 2)
 #pragma unroll
     for (int i = 0; i < IB; ++i) {
       if (i >= nbi) break;
@@ -1363,7 +1372,12 @@ __global__ void __launch_bounds__(256, IB * C > 6 ? 2 : 3) legendre_split_kernel
   for (int c = 0; c < C; ++c) xj[c] = lane + 64 * c < h ? xj[c] : 0.0;
   __syncthreads();
 
-  if (A.mode != 2) {
+  double2 gE[C][IB], gO[C][IB];
+#pragma unroll
+  for (int c = 0; c < C; ++c)
+#pragma unroll
+    for (int i = 0; i < IB; ++i) gE[c][i] = gO[c][i] = make_double2(0.0, 0.0);
+  if (ONE || A.mode != 2) {
     double2 yE[C][IB], yO[C][IB];
 #pragma unroll
     for (int c = 0; c < C; ++c) {
@@ -1387,18 +1401,20 @@ __global__ void __launch_bounds__(256, IB * C > 6 ? 2 : 3) legendre_split_kernel
       R1[c] = v.x;
       R2[c] = v.y;
     }
-    const int nblk = (r_hi - r_lo + RB - 1) / RB;  // this wave's blocks in each of the two passes
-    int left = 2 * nblk;
+    const int nblk = (r_hi - r_lo + RB - 1) / RB;  // this wave's blocks in a pass
+    int left = ONE ? nblk : 2 * nblk;
     constexpr int SH = NV == 32 ? 1 : 2;  // lanes per reduced value after the transpose-reduction
     // this lane's heat multiplier for row r0 + (its row in the block): loaded
     // at the start of each block, used after the block's arithmetic (rows past
     // the order's end read the array's padding and are dropped)
     const int hoff = (A.item0 + ib0 + min(((lane >> SH) >> 1) % IB, nbi - 1)) * A.hl_stride + m +
                      ((lane >> SH) >> 1) / IB;
+    T hln = A.hl[hoff + r_lo];
     for (int r0 = r_lo; r0 < r_hi; r0 += RB) {
       prio_by_blocks(left--);
-      const T hlv = A.hl[hoff + r0];
-      double acc[V];
+      const T hlv = ONE ? hln : A.hl[hoff + r0];
+      if (ONE) hln = A.hl[hoff + r0 + RB];  // a block is shorter than the load: one ahead
+      double acc[V], Rv[ONE ? RB : 1][C];
 #pragma unroll
       for (int v = 0; v < V; ++v) acc[v] = 0.0;
       const double* cfr = cf + (r0 - P.r_lo) + 1;  // coefficient of the next row
@@ -1407,6 +1423,7 @@ __global__ void __launch_bounds__(256, IB * C > 6 ? 2 : 3) legendre_split_kernel
         const double cn = cfr[rr];
 #pragma unroll
         for (int c = 0; c < C; ++c) {
+          if constexpr (ONE) Rv[rr][c] = R1[c];
 #pragma unroll
           for (int i = 0; i < IB; ++i) {
             const double2 y = (rr & 1) ? yO[c][i] : yE[c][i];  // every range starts on an even row
@@ -1427,7 +1444,7 @@ __global__ void __launch_bounds__(256, IB * C > 6 ? 2 : 3) legendre_split_kernel
         if (r < r_hi && i < nbi) {
           const int q = r - P.r_lo;
           const double g = gm[q];
-          if (A.mode == 0) {
+          if (ONE || A.mode == 0) {
             const double sc = g * g * (double)hlv;
             reinterpret_cast<double*>(&bs[(size_t)i * maxpl + q])[comp] = (double)s * sc;
           } else {
@@ -1436,8 +1453,25 @@ __global__ void __launch_bounds__(256, IB * C > 6 ? 2 : 3) legendre_split_kernel
           }
         }
       }
+      if constexpr (ONE) {  // the block's own rows (rows past the range are zero)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+        for (int rr = 0; rr < RB; ++rr)
+#pragma unroll
+          for (int i = 0; i < IB; ++i) {
+            const double2 b = bs[(size_t)i * maxpl + r0 - P.r_lo + rr];
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+              double2& G = (rr & 1) ? gO[c][i] : gE[c][i];
+              G.x = fma(Rv[rr][c], b.x, G.x);
+              G.y = fma(Rv[rr][c], b.y, G.y);
+            }
+          }
+      }
     }
-    if (A.mode == 1) return;
+    if (!ONE && A.mode == 1) return;
   } else {
     for (int i = 0; i < nbi; ++i)
       for (int q = tid; q < len; q += 256) {
@@ -1445,55 +1479,55 @@ __global__ void __launch_bounds__(256, IB * C > 6 ? 2 : 3) legendre_split_kernel
         bs[(size_t)i * maxpl + q] = make_double2((double)c.x * gm[q], (double)c.y * gm[q]);
       }
   }
-  // the synthesis pass restarts from the same checkpoints: issue their loads
-  // before the barrier so that they arrive while the workgroup's waves meet
-  {
-    const int ln = opaque_index(lane);
+  if constexpr (!ONE) {
+    // the synthesis pass restarts from the same checkpoints: issue their loads
+    // before the barrier so that they arrive while the workgroup's waves meet
+    {
+      const int ln = opaque_index(lane);
 #pragma unroll
-    for (int c = 0; c < C; ++c) ck[c] = ck_load(c, ln);
-  }
-  __syncthreads();
+      for (int c = 0; c < C; ++c) ck[c] = ck_load(c, ln);
+    }
+    __syncthreads();
 
-  // synthesis over this wave's rows: G^{E|O}_m(j) += (b_l gamma_l) R_l(x_j)
-  double2 gE[C][IB], gO[C][IB];
-  double R1[C], R2[C];
+    // synthesis over this wave's rows: G^{E|O}_m(j) += (b_l gamma_l) R_l(x_j)
+    double R1[C], R2[C];
 #pragma unroll
-  for (int c = 0; c < C; ++c) {
-    const double2 v = ck_use(ck[c], c);
-    R1[c] = v.x;
-    R2[c] = v.y;
+    for (int c = 0; c < C; ++c) {
+      const double2 v = ck_use(ck[c], c);
+      R1[c] = v.x;
+      R2[c] = v.y;
+    }
+    int left = (r_hi - r_lo + 15) / 16;
+    for (int r0 = r_lo; r0 < r_hi; r0 += 16) {
+      prio_by_blocks(left--);
+      const int q0 = r0 - P.r_lo;
 #pragma unroll
-    for (int i = 0; i < IB; ++i) { gE[c][i] = make_double2(0.0, 0.0); gO[c][i] = make_double2(0.0, 0.0); }
-  }
-  int left = (r_hi - r_lo + 15) / 16;
-  for (int r0 = r_lo; r0 < r_hi; r0 += 16) {
-    prio_by_blocks(left--);
-    const int q0 = r0 - P.r_lo;
+      for (int rr = 0; rr < 16; ++rr) {
+        const double cn = cf[q0 + rr + 1];
+        double2 b[IB];
 #pragma unroll
-    for (int rr = 0; rr < 16; ++rr) {
-      const double cn = cf[q0 + rr + 1];
-      double2 b[IB];
+        for (int i = 0; i < IB; ++i) b[i] = bs[(size_t)i * maxpl + q0 + rr];
 #pragma unroll
-      for (int i = 0; i < IB; ++i) b[i] = bs[(size_t)i * maxpl + q0 + rr];
+        for (int c = 0; c < C; ++c) {
 #pragma unroll
-      for (int c = 0; c < C; ++c) {
-#pragma unroll
-        for (int i = 0; i < IB; ++i) {
-          if (rr & 1) {
-            gO[c][i].x = fma(R1[c], b[i].x, gO[c][i].x);
-            gO[c][i].y = fma(R1[c], b[i].y, gO[c][i].y);
-          } else {
-            gE[c][i].x = fma(R1[c], b[i].x, gE[c][i].x);
-            gE[c][i].y = fma(R1[c], b[i].y, gE[c][i].y);
+          for (int i = 0; i < IB; ++i) {
+            if (rr & 1) {
+              gO[c][i].x = fma(R1[c], b[i].x, gO[c][i].x);
+              gO[c][i].y = fma(R1[c], b[i].y, gO[c][i].y);
+            } else {
+              gE[c][i].x = fma(R1[c], b[i].x, gE[c][i].x);
+              gE[c][i].y = fma(R1[c], b[i].y, gE[c][i].y);
+            }
           }
+          const double rn = fma(cn * xj[c], R1[c], R2[c]);
+          R2[c] = R1[c];
+          R1[c] = rn;
         }
-        const double rn = fma(cn * xj[c], R1[c], R2[c]);
-        R2[c] = R1[c];
-        R1[c] = rn;
       }
     }
   }
   __builtin_amdgcn_s_setprio(0);
+  if constexpr (ONE) __syncthreads();  // every wave has read its spectra, whose place the sums take
   // combine the four waves' partial sums (fixed order)
 #pragma unroll
   for (int c = 0; c < C; ++c) {
@@ -2854,7 +2888,17 @@ template <typename T, int IB, int C>
 static hipError_t launch_split(const LegArgs<T>& a, hipStream_t stream) {
   dim3 grid(a.nparts, (a.nb + IB - 1) / IB);
   const size_t lds = split_lds_bytes(a.maxlen, a.h, IB, (int)sizeof(T));
-  SHOT_LAUNCH((legendre_split_kernel<T, IB, C, 32>), grid, dim3(256), lds, stream, a);
+  // one pass up to 3 chains of one item or one of two items per lane; beyond, the
+  // values kept for the second half of a block cost a resident wave or shorter
+  // blocks, and two passes are faster (6 chains at L = 720: 39.7 against 44.5 us;
+  // 2 items of 2 chains at L = 180: 11.4 either way)
+  if constexpr (IB == 1 ? C <= 3 : C == 1) {
+    if (a.mode == 0) {
+      SHOT_LAUNCH((legendre_split_kernel<T, IB, C, 16 * IB, true>), grid, dim3(256), lds, stream, a);
+      return hipGetLastError();
+    }
+  }
+  SHOT_LAUNCH((legendre_split_kernel<T, IB, C, 32, false>), grid, dim3(256), lds, stream, a);
   return hipGetLastError();
 }
 
