@@ -255,7 +255,8 @@ shot_status shot_gradient_regional_rms(shot_plan_t plan, const int32_t* grid_of_
  * recurrence-fed matrix-core kernel with that many items per workgroup, which
  * bfloat16 plans always use) and, as the second value, for SHOT_LEG_RECURRENCE grids the latitude chains
  * per thread of the latitude-split kernel (1, 2 or 4, at most 256 threads per
- * workgroup; 0 = the row-split kernel), for SHOT_LEG_TABLE grids of float32 and
+ * workgroup; 0 = the row-split kernel, and with both values 0 float64 matrix
+ * cores for batches of grids of at most 768 rows), for SHOT_LEG_TABLE grids of float32 and
  * bfloat16 plans the matrix-core kernel's column tiles per workgroup (1, 2 or 4
  * tiles of 16 columns = 8, 16 or 32 items; float32 grids of at most 1024 rows
  * always take 8; 0 = automatic: matrix cores for any

@@ -35,7 +35,8 @@
 namespace shot {
 
 // ---------------------------------------------------------------------------
-// Row kernel.  grid = (ceil(h / RPW) groups of RPW row pairs, items), block 256.
+// Row kernel: the modes and sizes that row_wave_kernel does not run.  grid =
+// (ceil(h / RPW) groups of RPW row pairs, items; RPW = 1 in every launch), block 256.
 // Each row pair (j, nlat-1-j) rides in one complex FFT; the RPW pairs of a
 // group share the twiddles and the barriers of the staged FFTs, and their
 // spectral entries (m, j..j+RPW-1) are contiguous in memory.  Per-row-pair
@@ -557,8 +558,9 @@ __global__ void __launch_bounds__(BS) row_kernel(RowArgs<T> A) {
 }
 
 // ---------------------------------------------------------------------------
-// Sinkhorn half-iteration row kernel (modes ROW_SINK_U / ROW_SINK_V), the hot
-// path of every solve.  Same arithmetic as row_kernel, organised for latency:
+// Sinkhorn half-iteration row kernel (modes ROW_SINK_U / ROW_SINK_V) of float
+// rows of 1440 points, and of 180, 360 and 720 below 1024 pairs a launch (beyond,
+// and for other lengths, row_wave_kernel).  Same arithmetic as row_kernel, organised for latency:
 // every global load of the workgroup (spectral gather, marginal, previous u,
 // partial sums) is issued before the inverse FFT; the block reductions ride on
 // the barriers the FFT needs anyway (wave partials in LDS, combined by one

@@ -342,6 +342,9 @@ __device__ __forceinline__ T quotient(T f, T kv) {
 }
 
 enum RowKind : int { RK_FWD, RK_INV, RK_SINK, RK_ADJ, RK_ADJU_V1, RK_ADJU_B, RK_ADJU_A };
+// RK_SINK with it keeps the gauge for the reverse sweep: a kernel of its own, as
+// the store costs the 720-point one, which is at its register limit, 1 us of 35
+constexpr int RK_KEEP = 16;
 
 // Everything a pair's pointwise step reads, and the sums it keeps.
 template <typename T>
@@ -511,11 +514,12 @@ constexpr int row_waves(int real_bytes, int nc, int kind) {
 // NC > 0: compile-time row length, NPC pairs per workgroup.  NC == 0: run-time
 // length or HEALPix rings, blockDim / TP pairs per workgroup; TP > 64: one
 // pair per workgroup, stages separated by workgroup barriers.
-template <typename T, int NC, int TP, int NPC, int KIND>
-__global__ void __launch_bounds__(NC > 0 ? TP * NPC : (TP > 64 ? TP : 256), row_waves(sizeof(T), NC, KIND))
+template <typename T, int NC, int TP, int NPC, int KX>
+__global__ void __launch_bounds__(NC > 0 ? TP * NPC : (TP > 64 ? TP : 256), row_waves(sizeof(T), NC, KX % RK_KEEP))
 row_wave_kernel(RowArgs<T> A) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  constexpr bool CT = NC > 0;
+  constexpr int KIND = KX % RK_KEEP;
+  constexpr bool CT = NC > 0, KEEP = KX >= RK_KEEP;
   constexpr bool INV = KIND != RK_FWD && KIND != RK_ADJU_B;           // has the inverse transform
   constexpr bool FWD = KIND != RK_INV && KIND != RK_ADJU_V1;          // has the forward transform
   const int bs = CT ? TP * NPC : (int)blockDim.x;
@@ -729,7 +733,7 @@ row_wave_kernel(RowArgs<T> A) {
           b += shw[w][1];
         }
         S.g = I.balanced ? a : exp(-(0.5 * I.tau * (log(a) - log(b))) / I.eps);
-        if (blockIdx.x == 0 && tid == 0) store_gauge(A, it, S.g, a, b);
+        if (KEEP && blockIdx.x == 0 && tid == 0) store_gauge(A, it, S.g, a, b);
       }
       S.gs = (T)S.g;
     }
@@ -1101,7 +1105,7 @@ hipError_t launch_rows_wave(const RowArgs<T>& a, int nb, const RowWaveShape& w, 
   switch (kind_of(a.mode, a.k >= a.kT, a.in != nullptr)) {
     case RK_FWD: return launch_kind<T, RK_FWD>(a, nb, w, stream);
     case RK_INV: return launch_kind<T, RK_INV>(a, nb, w, stream);
-    case RK_SINK: return launch_kind<T, RK_SINK>(a, nb, w, stream);
+    case RK_SINK: return a.gout ? launch_kind<T, RK_SINK | RK_KEEP>(a, nb, w, stream) : launch_kind<T, RK_SINK>(a, nb, w, stream);
     case RK_ADJ: return launch_kind<T, RK_ADJ>(a, nb, w, stream);
     case RK_ADJU_V1: return launch_kind<T, RK_ADJU_V1>(a, nb, w, stream);
     case RK_ADJU_B: return launch_kind<T, RK_ADJU_B>(a, nb, w, stream);
