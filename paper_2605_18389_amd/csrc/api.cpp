@@ -896,7 +896,8 @@ bool use_t64(const GridRec& g) {
 
 // Recurrence-fed float64 matrix-core kernel (8 items per workgroup) instead of
 // the row-split kernel, where no tuning asks for one: from three row-split item
-// chunks per chunk of 8 on, and from 1024 row-split workgroups on (they are
+// pairs per chunk of 8 on (five items where it runs them singly: 721x1440, 4 items
+// 165 -> 190 us, 6 items 241 -> 191), and from 1024 row-split workgroups on (they are
 // resident 768 at a time).  Heat apply of float32 plans, row-split -> this, us:
 // below the line 8 items at 128x256 9.8 -> 10.1, 4 at 256x512 17.4 -> 21.5, 8 at
 // 180x360 15.3 -> 16.2, 10 at 360x720 65 -> 72; above it 16 at 128x256 13.0 ->
@@ -906,7 +907,7 @@ bool use_r64(const shot_plan_s* P, const GridRec& g, int nb, int leg_mode) {
   if (g.tab_kind != TAB_RECUR || g.tune_ib != 0 || g.tune_jpt != 0 || !r64_fits(g.d.L, g.h)) return false;
   if (rmma_tiles(P, g, nb, leg_mode, nullptr) > 0) return false;
   const int ib = split_ib(P, g, nb), chunks = (nb + ib - 1) / ib;
-  return chunks >= 3 * ((nb + 7) / 8) && g.d.L * chunks >= 1024;
+  return chunks >= (ib == 1 ? 5 : 3) * ((nb + 7) / 8) && g.d.L * chunks >= 1024;
 }
 
 template <typename T>
