@@ -438,18 +438,6 @@ shot_status build_grid(shot_plan_s* P, GridRec& g, int leg_mode, hipStream_t s) 
     g.tab_kind = TAB_RECUR;
     std::vector<double> coef, gam, seed;
     legendre_recurrence_data(d.L, xs, coef, gam, seed);
-    if (P->prec == SHOT_FP32) {
-      // The matrix-core kernel rounds the recurrence's values to float32.  For
-      // degree 0 that is one number for every latitude, 1/sqrt(4 pi), whose
-      // rounding (5e-8, the same sign in both transforms of every apply) scales
-      // the operator's constant mode and adds up over a solve and its adjoint:
-      // run the recurrence on sqrt(4 pi) P̄ instead, whose degree 0 is 1 (with the
-      // kernel's float64 degree-0 sum, the gradient of 8 pairs at 360x720 over 40
-      // iterations: error against float64 1.5e-5 -> 6e-6 for the worst of six inputs)
-      const double s4 = std::sqrt(4.0 * M_PI);
-      for (auto& v : seed) v *= s4;
-      for (auto& v : gam) v /= s4;
-    }
     const unsigned hw = std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
     // Row-split work lists: whole orders, and, for grids whose longest order
     // does not fit the kernel's LDS, orders cut into the longest parts that do.

@@ -2299,8 +2299,11 @@ legendre_rmma_kernel(LegArgs<T> A) {
   // sensitive (gradient of 8 pairs at 360x720, worst of 6 inputs: error against
   // float64 2.0e-5 with f_00 from the float32 products).
   double* zs = reinterpret_cast<double*>(smem_raw + Q.o_z);
-  // a float32 table holds P̄_0^0 rounded: f_00 takes the exact value, and b_00 the
-  // ratio of the two, so that the rounding leaves the operator's constant mode
+  // The table and the rows below hold P̄_0^0 = 1/sqrt(4 pi) rounded to float32 (5e-8
+  // off, the same way in every apply of a solve and its adjoint): f_00 takes the
+  // exact value, and b_00 the ratio of the two, so that the rounding leaves the
+  // operator's constant mode.  (A recurrence run on sqrt(4 pi) P̄, whose degree 0 is
+  // 1, does the same here, but cost the row-split kernel a rounding of f_00.)
   constexpr double P00 = 0.28209479177387814347;
   constexpr double p00fix = P00 / (double)(float)P00;
   if constexpr (OP == RM_F32) {
@@ -2466,7 +2469,7 @@ legendre_rmma_kernel(LegArgs<T> A) {
       if (OP == RM_F32 && m == 0 && r0 == 0 && par == 0 && q4 == 0) {
         double z = 0.0;
         for (int w = 0; w < nw; ++w) z += zs[w * NC + n];
-        o[0] = SRC == RM_TABLE ? (float)(z * P00 * sc[0] * (mode == 0 ? p00fix : 1.0)) : (float)(z * A.rseed[0] * sc[0]);
+        o[0] = (float)(z * P00 * sc[0] * (mode == 0 ? p00fix : 1.0));
       }
       if (SRC == RM_TABLE && mode == 1) {
 #pragma unroll

@@ -1,0 +1,51 @@
+"""Float32 errors against the float64 plan on the same inputs, over enough inputs that a launch's rounding luck
+averages out.  u = 2^-24 is the unit roundoff of float32."""
+
+import numpy as np
+import pytest
+
+from helpers import announce, ensure_built
+
+pytestmark = pytest.mark.gpu
+
+U = 2.0 ** -24
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _built():
+    ensure_built()
+
+
+def _plans(grid):
+    from paper_2605_18389_amd import Plan
+    return (Plan([grid], precision=p, legendre="recurrence") for p in ("fp32", "fp64"))
+
+
+def _field(P, seed):
+    """A float32 field around a mean anywhere in a binade, so that sums of any mantissa are met."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    mean = 2.0 ** torch.rand(1, dtype=torch.float64, device="cuda", generator=g)
+    return (mean * (0.5 + torch.rand(P.field_size(0), dtype=torch.float64, device="cuda", generator=g))).float()
+
+
+def _rms(x):
+    return float(np.sqrt(np.mean(np.square(x))))
+
+
+@pytest.mark.parametrize("grid", [("gl", 200, 400, 200), ("gl", 256, 512, 256), ("gl", 512, 1024, 512),
+                                  ("cc", 721, 1440, 720)])
+def test_mean_of_one_field(grid):
+    """f_00 of one item (row-split kernel): float64 lane sums, a float32 tree over the lanes, one rounding of the
+    result.  A rounding of a mantissa anywhere in its binade is off by 0.425 u rms; the tree's levels carry half
+    the weight each, which makes sqrt(2) of that: 0.60 u, and 10 % for 64 samples.  A second rounding of the
+    result (0.425 u more, in quadrature: 0.74 u) is over it."""
+    announce(f"mean of one field {grid}")
+    P, D = _plans(grid)
+    e = []
+    for seed in range(64):
+        x = _field(P, seed)
+        c, d = complex(P.analysis(x)[0]), complex(D.analysis(x.double())[0])
+        e.append(abs(c - d) / abs(d))
+    assert _rms(e) < 0.66 * U, _rms(e) / U
