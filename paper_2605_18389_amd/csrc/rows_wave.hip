@@ -336,9 +336,11 @@ __device__ __forceinline__ void track_range(T& mn, T& mx, T v) {
   mx = sizeof(T) == 4 ? (T)fmaxf((float)mx, (float)d) : (T)fmax((double)mx, (double)d);
 }
 
-// Quotient of the Sinkhorn update.  FAST (compile-time float rows): hardware
-// reciprocal and one Newton step, about 1 ulp, as row_sink_kernel; an IEEE
-// divide below the smallest normal float.
+// Quotient of the Sinkhorn update.  FAST (float rows of 180, 360 and 720 points):
+// hardware reciprocal and one Newton step, about 1 ulp, as row_sink_kernel runs them
+// in smaller launches; an IEEE divide below the smallest normal float.  Every other
+// length divides exactly, as row_kernel does: the reciprocal of a value above 2^126
+// is not a normal float and would make the scaling 0.
 template <typename T, bool FAST>
 __device__ __forceinline__ T quotient(T f, T kv) {
   if constexpr (FAST && sizeof(T) == 4) {
@@ -801,7 +803,7 @@ row_wave_kernel(RowArgs<T> A) {
           }
         } else {
           T nv[2];
-          point<T, KIND, true>(A, I, S, PREF ? col[i][r] : load_col<T, KIND>(A, I, S, c), c, INV ? v[i][r] : cpx<T>{(T)0, (T)0}, nv);
+          point<T, KIND, NC % 180 == 0>(A, I, S, PREF ? col[i][r] : load_col<T, KIND>(A, I, S, c), c, INV ? v[i][r] : cpx<T>{(T)0, (T)0}, nv);
           v[i][r] = {nv[0], nv[1]};
         }
       }

@@ -93,3 +93,19 @@ def test_rings_of_long_primes(nside):
         c, d = P.analysis(x)[1:].to(dtype=D.analysis(x.double()).dtype), D.analysis(x.double())[1:]
         e.append(float((c - d).norm() / d.norm()))
     assert _rms(e) < 1.25 * {251: 7.9e-7, 401: 1.07e-6, 509: 1.23e-6}[nside], _rms(e)
+
+
+@pytest.mark.parametrize("nlon", [64, 128, 256, 512, 1024])
+def test_divide_by_large_kernel_values(nlon):
+    """Marginals of a scale that takes the gauge times K v to 1.5e38, above 2^126, whose reciprocal is subnormal,
+    while every scaling stays a normal number.  As the float64 solve, to the transforms' rounding: a few u in each
+    of the four halves."""
+    announce(f"divide by large kernel values {nlon}")
+    P, D = _plans(("gl", 1024 * 64 // nlon, nlon, 8))
+    p, q = ((x / x.mean() * (1.5e38 / P.field_size(0))).float() for x in (_field(P, k).double() for k in (1, 2)))
+    # u-hat_1 = p, its sum g = 1.5e38, v-hat_1 = q / p, and u-hat_2 = p / (g K v-hat_1)
+    phi, psi, info = P.sinkhorn(p, q, 4.0, T=2)
+    dphi, dpsi, dinfo = D.sinkhorn(p.double(), q.double(), 4.0, T=2)
+    assert info[0]["breakdown_iter"] == 0 and dinfo[0]["breakdown_iter"] == 0
+    assert float((phi.double() - dphi).norm() / dphi.norm()) < 20 * U
+    assert float((psi.double() - dpsi).norm() / dpsi.norm()) < 20 * U
