@@ -934,7 +934,9 @@ row_wave_kernel(RowArgs<T> A) {
         A.adjp[(size_t)it * A.hs + j] = fst ? r4[0] : 0.0;
       }
     }
-    if (anybad && lane == 0) atomicMin(&A.brk[it], A.k);
+    // (read first: once an item has broken down every wave of every later half is bad, and
+    // their atomics on its one word took 8 us a half of 361 float64 pairs)
+    if (anybad && lane == 0 && A.brk[it] > A.k) atomicMin(&A.brk[it], A.k);
   }
   if constexpr (!FWD) return;
 
