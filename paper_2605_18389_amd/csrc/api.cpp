@@ -47,6 +47,7 @@ struct GridRec {
   std::vector<double> aw_host;  // area weight of each row pair, double precision
   std::vector<int> fac;
   RingDev* d_rowfft = nullptr;       // latitude-longitude grids: the row length's radices
+  int row_pad = 0;                   // latitude-longitude grids: padding entries of the first run-time stage
   int tab_kind = TAB_F32;
   void* d_tab = nullptr;
   int* d_morder = nullptr;           // [L] order run by MFMA workgroup column b (rows balanced over units)
@@ -260,6 +261,7 @@ shot_status build_grid(shot_plan_s* P, GridRec& g, int leg_mode, hipStream_t s) 
     R.nfac = (int)f.size();
     std::copy(f.begin(), f.end(), R.fac);
     std::copy(mg.begin(), mg.end(), R.mg);
+    g.row_pad = f.size() > 1 && f[0] % 4 == 0 ? d.nlon / f[0] : 0;
     const shot_status sr = upload((void**)&g.d_rowfft, std::vector<RingDev>{R}, s);
     if (sr != SHOT_OK) return sr;
   }
@@ -734,6 +736,7 @@ RowArgs<T> row_args(const shot_plan_s* P, const GridRec& g, const Layout& Lo, co
   a.nfac = (int)g.fac.size();
   for (int i = 0; i < a.nfac && i < 8; ++i) a.fac[i] = g.fac[i];
   a.rowfft = g.d_rowfft;
+  a.row_pad = g.hp ? g.d.nlon / 4 : g.row_pad;
   a.max_prime = g.fac.empty() ? 0 : *std::max_element(g.fac.begin(), g.fac.end());
   a.tw = static_cast<const cpx<T>*>(g.d_tw);
   a.aw = static_cast<const T*>(g.d_aw);

@@ -987,8 +987,8 @@ static int wave_stride_ct(int n, int first_radix_pad, int mod) {
   while (w % 32 != mod) ++w;
   return w;
 }
-static int wave_stride_rt(const int nbuf, int need) {
-  int w = std::max({nbuf + nbuf / 4, need, 64});
+static int wave_stride_rt(int nbuf, int pad, int need) {
+  int w = std::max({nbuf + pad, need, 64});
   while (w % 16 != 4) ++w;
   return w;
 }
@@ -1027,7 +1027,7 @@ static hipError_t launch_ct(RowArgs<T> a, int nb, int mod, hipStream_t stream) {
 
 template <typename T, int TP, int KIND>
 static hipError_t launch_rt(RowArgs<T> a, int nb, int np, hipStream_t stream) {
-  a.wstride = wave_stride_rt(a.nlon, std::max(a.ring ? 2 * a.L : 0, TP));
+  a.wstride = wave_stride_rt(a.nlon, a.row_pad, std::max(a.ring ? 2 * a.L : 0, TP));
   const size_t lds = ((size_t)np * 2 * a.wstride + (size_t)(a.ring ? np : 1) * a.nlon) * sizeof(cpx<T>);
   static size_t enabled = 65536;
   hipError_t e = allow_lds(&row_wave_kernel<T, 0, TP, 1, KIND>, lds, enabled);
@@ -1107,9 +1107,17 @@ RowWaveShape row_wave_shape(const RowArgs<T>& a, int nb) {
   const bool narrow = a.ring ? (a.nlon <= 128 || (a.nlon <= 256 && pairs >= 512)) : (a.nlon <= 256 && a.max_prime <= 13);
   w.tp = narrow ? 64 : 256;
   w.np = 1;
-  const int ws = wave_stride_rt(a.nlon, std::max(a.ring ? 2 * a.L : 0, w.tp));
+  const int ws = wave_stride_rt(a.nlon, a.row_pad, std::max(a.ring ? 2 * a.L : 0, w.tp));
   auto lds = [&](int np) { return ((size_t)np * 2 * ws + (size_t)(a.ring ? np : 1) * a.nlon) * sizeof(cpx<T>); };
   if (lds(1) > 150 * 1024) return RowWaveShape{0, 0, 0};  // band limits far beyond a ring's length
+  // float64 rows whose buffers leave room for one workgroup a compute unit where
+  // row_kernel's (smaller by the padding) leave room for two: row_kernel (one item of
+  // 1600 points: 33.6 against 42.2 us a Sinkhorn half; 1500 points 30.3 against 40.7;
+  // 1536 and 1440 points fit twice: 26.8 and 26.6 against 34.1 and 31.8).  A prime
+  // above 5 costs row_kernel more than that.
+  if (!a.ring && a.max_prime <= 5 && lds(1) + 1024 > 80 * 1024 &&
+      (size_t)3 * a.nlon * sizeof(cpx<T>) + 5 * 1024 <= 80 * 1024)
+    return RowWaveShape{0, 0, 0};
   if (w.tp == 64) {
     // four neighbouring pairs per workgroup while the launch keeps 512 workgroups
     w.np = 4;

@@ -85,6 +85,7 @@ struct RowArgs {
   const RingDev* rowfft;
   int wstride;
   int max_prime;      // largest prime factor of a latitude-longitude grid's row length
+  int row_pad;        // entries of padding that a run-time length's first stage writes
   const int* rpair;   // ring grids: ring pair run by workgroup column b (nullptr: xcd_row_pair order)
   cpx<T>* spec;
   int mode;

@@ -1,0 +1,50 @@
+"""Row transforms on both sides of the lines between their launch forms, against the oracle: heat applies, solves and
+gradients of few and many row pairs, balanced and unbalanced."""
+
+import math
+
+import numpy as np
+import pytest
+
+import oracle as O
+
+from helpers import announce, ensure_built, rel_l2, to_dev, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _built():
+    ensure_built()
+
+
+def _check(grid, items, precision, taus=(math.inf,), gradient=False):
+    from paper_2605_18389_amd import Plan
+    announce(f"row lines {grid} x{items} {precision}")
+    G = O.HealpixGrid(grid[1], grid[2]) if grid[0] == "hp" else O.make_grid(*grid)
+    rng = np.random.default_rng(items)
+    p, q = (0.5 + rng.random((items,) + tuple(G.field_shape)) for _ in range(2))
+    tol = 1e-5 if precision == "fp32" else 1e-12
+    P = Plan([grid], precision=precision, legendre="recurrence")
+    pd, qd = to_dev(p, P.dtype), to_dev(q, P.dtype)
+    pick = sorted({0, items // 2, items - 1})
+    for tr in (False, True):
+        out = to_np(P.heat_apply(pd, 1e-3, transpose=tr)).reshape(p.shape)[pick]
+        assert rel_l2(out, O.heat_apply(p[pick], G, 1e-3, transpose=tr)) < tol
+    for tau in taus:
+        phi, psi, info = P.sinkhorn(pd, qd, 0.5, tau, T=3, C=2)
+        r = O.sinkhorn(p[pick], q[pick], G, 0.5, tau, T=3, C=2)
+        assert rel_l2(to_np(phi).reshape(p.shape)[pick], r["phi"]) < 10 * tol
+        assert rel_l2(to_np(psi).reshape(p.shape)[pick], r["psi"]) < 10 * tol
+        assert all(info[i]["status"] == 0 for i in pick)
+        if gradient:  # a batch against its last pair's own call
+            g = to_np(P.divergence_grad(pd, qd, 0.5, T=3, tau=tau)[1]).reshape(p.shape)
+            one = to_np(P.divergence_grad(to_dev(p[-1], P.dtype), to_dev(q[-1], P.dtype), 0.5, T=3, tau=tau)[1])
+            assert rel_l2(g[-1], one.reshape(p[-1].shape)) < 20 * tol
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("nlon", [1440, 1458, 1500, 1536, 1599, 1600, 1602, 1620, 2000, 2048])
+def test_long_rows(nlon, precision):
+    """Lengths whose float64 buffers fit a compute unit's LDS twice or once, of radix 8, 4, 2 and 3 first."""
+    _check(("gl", 7, nlon, 7), 2, precision, gradient=True)
