@@ -1077,6 +1077,8 @@ shot_status solve_impl(shot_plan_s* P, const SolveSpec& S, T* phi, T* psi, shot_
     tv[i] = S.prm[i].eps / 4.0;  // t = eps/4 (Alg. 1)
   }
   ST_TRY(upload_items<T>(P, Lo, S.grid.data(), eps, tau, tv, S.p, S.q, W, s));
+  // (chooses the float64 row kernels: part of a recorded graph's key)
+  const bool unbal = std::any_of(tau.begin(), tau.end(), [](double x) { return !std::isinf(x); });
 
   auto each_group = [&](auto&& fn) -> shot_status {
     for (const Group& G : Lo.groups) {
@@ -1089,6 +1091,7 @@ shot_status solve_impl(shot_plan_s* P, const SolveSpec& S, T* phi, T* psi, shot_
   auto rows = [&](const Group& G, const GridRec& g, int mode, int k, int chk) {
     RowArgs<T> a = row_args<T>(P, g, Lo, G, W, nitems);
     a.mode = mode;
+    a.unbal = unbal;
     a.k = k;
     a.chk_slot = chk;
     a.out = phi;
@@ -1173,7 +1176,7 @@ shot_status solve_impl(shot_plan_s* P, const SolveSpec& S, T* phi, T* psi, shot_
   // (event timing needs eager launches: events recorded inside a graph cannot be timed)
   if (tol == 0 && P->graphs && !P->prof) {
     std::vector<long long> key = {(long long)(uintptr_t)P->ws.p, (long long)P->ws.bytes, nitems, T_iter, C,
-                                  Lo.hs, Lo.Lmax, P->prof ? 1 : 0};
+                                  Lo.hs, Lo.Lmax, P->prof ? 1 : 0, unbal ? 1 : 0};
     for (const Group& G : Lo.groups) {
       key.push_back(G.grid);
       key.push_back(G.first);
@@ -1528,6 +1531,7 @@ shot_status adjoint_impl(shot_plan_s* P, const SolveSpec& S, int CK, T** pbar_ou
     a.gB = gB;
     a.adjp = adjp;
     a.kT = Tit;
+    a.unbal = unbal;
     a.vbar = vbar;
     return a;
   };

@@ -1082,9 +1082,20 @@ RowWaveShape row_wave_shape(const RowArgs<T>& a, int nb) {
   const int kind = kind_of(a.mode, a.k >= a.kT, a.in != nullptr);
   if (kind < 0) return w;
   const long long pairs = (long long)a.h * nb;
+  // Powers: the unbalanced reverse steps, and in float64 the unbalanced halves (about 150
+  // instructions each).  Float64 rows of compile-time lengths whose launch does not fill
+  // the device take the run-time form with more lanes a pair (one item, a Sinkhorn half:
+  // 512 points 16.0 us with 256 lanes against 23.4 with 64, 256 points 13.0 against 14.0;
+  // 64 points 10.4 with 64 lanes against 12.7 with 16), of 1024 points always (1536 pairs:
+  // 112 us in the compile-time form, whose LDS leaves one workgroup a compute unit,
+  // against 85).  Above the lines: 512 points, 1024 pairs 30.5 us against 32.1; 256
+  // points, 512 pairs 15.4 against 16.2.
+  const bool powers = kind == RK_ADJU_B || kind == RK_ADJU_A || (sizeof(T) == 8 && a.unbal && kind == RK_SINK);
+  const bool shared = sizeof(T) == 8 && powers &&
+                      (a.nlon == 1024 || pairs < (a.nlon == 128 || a.nlon == 256 ? 400 : 900));
   const bool pow2 = a.nlon == 64 || a.nlon == 128 || a.nlon == 256 || a.nlon == 512 || (a.nlon == 1024 && pairs >= 1024);
   const bool deg = sizeof(T) == 4 && (a.nlon == 180 || a.nlon == 360 || a.nlon == 720);
-  if (!a.ring && (pow2 || deg)) {
+  if (!a.ring && !shared && (pow2 || deg)) {
     // 64 to 1024 points: always (one item of 256 points: 12.8 -> 7.8 us in
     // float64; of 1024 points only with many pairs, the run-time form's 256
     // lanes are faster for one item: 15.1 against 16.9 us).  180, 360 and 720
@@ -1099,12 +1110,17 @@ RowWaveShape row_wave_shape(const RowArgs<T>& a, int nb) {
     return w;
   }
   if (!a.ring && sizeof(T) == 4 && a.nlon == 1440) return w;  // row_sink_kernel, 512 lanes
-  // run-time lengths: one wave per pair for short rows (192 points: 10.9 us
-  // against 11.5 with 256 lanes), 256 lanes for long ones (400 points: 15.1
-  // against 11.9) and for large primes; rings from 512 pairs on, where the
-  // launch fills the device (24 items at Nside 64: 23.9 against 37.4 us; one
-  // item 16.6 against 11.9)
-  const bool narrow = a.ring ? (a.nlon <= 128 || (a.nlon <= 256 && pairs >= 512)) : (a.nlon <= 256 && a.max_prime <= 13);
+  // Run-time lengths: one wave per pair for rows of up to 200 points (192 points, one
+  // item, a half: 9.7 us; float64 10.6 against 11.2 with 256 lanes), of up to 256 points
+  // from 500 pairs on (240 points: one item 11.1 us against 10.2, 960 pairs reverse 14.7
+  // against 18.0), with powers beyond 128 points from 640 pairs on (240 points, float64
+  // half: one item 17.8 us against 13.2, 960 pairs 22.5 against 22.4); 256 lanes for
+  // longer rows (400 points: 15.1 against 11.9) and for large primes.  Rings from 512
+  // pairs on, where the launch fills the device (24 items at Nside 64: 23.9 against 37.4
+  // us; one item 16.6 against 11.9)
+  const int line = powers && a.nlon > 128 ? 640 : a.nlon > 200 ? 500 : 0;
+  const bool narrow = a.ring ? (a.nlon <= 128 || (a.nlon <= 256 && pairs >= 512))
+                             : a.max_prime <= 13 && a.nlon <= 256 && pairs >= line;
   w.tp = narrow ? 64 : 256;
   w.np = 1;
   const int ws = wave_stride_rt(a.nlon, a.row_pad, std::max(a.ring ? 2 * a.L : 0, w.tp));

@@ -118,6 +118,7 @@ struct RowArgs {
   int gstride;        // goes, gstride entries per item; nullptr: nowhere
   const double* gk;   // [nitems] SINK_U: gauge of iteration k-1 to use instead of the partial sums;
                       // adjoint modes: s of the iteration whose u-hat / v-hat are read
+  int unbal;          // an item of the call is unbalanced (finite tau)
   int kT;             // adjoint: last iteration T (its u-bar term enters ROW_ADJ_A)
   T* vbar;            // unbalanced adjoint: v-bar_k field (layout of fields)
   // spectrum written by a row-split Legendre launch that cut long orders into

@@ -48,3 +48,28 @@ def _check(grid, items, precision, taus=(math.inf,), gradient=False):
 def test_long_rows(nlon, precision):
     """Lengths whose float64 buffers fit a compute unit's LDS twice or once, of radix 8, 4, 2 and 3 first."""
     _check(("gl", 7, nlon, 7), 2, precision, gradient=True)
+
+
+@pytest.mark.parametrize("grid,items", [(("gl", 32, 64, 31), 1), (("gl", 32, 64, 31), 56), (("gl", 32, 64, 31), 57),
+                                        (("gl", 50, 128, 30), 15), (("gl", 50, 128, 30), 16), (("gl", 50, 256, 30), 15),
+                                        (("gl", 50, 256, 30), 16), (("gl", 60, 512, 30), 29), (("gl", 60, 512, 30), 30),
+                                        (("gl", 64, 1024, 30), 32), (("gl", 40, 240, 30), 31),
+                                        (("gl", 40, 240, 30), 32)])
+def test_float64_powers(grid, items):
+    """Balanced and unbalanced float64 steps below and from the pair count from which they share a form."""
+    _check(grid, items, "fp64", taus=(math.inf, 1.0), gradient=True)
+
+
+def test_balanced_and_unbalanced_on_one_plan():
+    """A recorded solve is replayed for calls of its own kind only: the same bits as on a plan of its own."""
+    import torch
+    from paper_2605_18389_amd import Plan
+    announce("balanced and unbalanced on one plan")
+    grid = ("gl", 20, 512, 20)
+    rng = np.random.default_rng(3)
+    one = Plan([grid], precision="fp64", legendre="recurrence")
+    p, q = (to_dev(0.5 + rng.random((20, 512)), one.dtype) for _ in range(2))
+    for tau in (math.inf, 1.0, math.inf, 10.0):
+        own = Plan([grid], precision="fp64", legendre="recurrence")
+        a, b = one.sinkhorn(p, q, 0.5, tau, T=5), own.sinkhorn(p, q, 0.5, tau, T=5)
+        assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1]) and a[2] == b[2]
