@@ -46,6 +46,7 @@ struct GridRec {
   std::vector<double> x, w;
   std::vector<double> aw_host;  // area weight of each row pair, double precision
   std::vector<int> fac;
+  int max_prime = 1;                 // largest prime factor of the (longest) row length
   RingDev* d_rowfft = nullptr;       // latitude-longitude grids: the row length's radices
   int row_pad = 0;                   // latitude-longitude grids: padding entries of the first run-time stage
   int tab_kind = TAB_F32;
@@ -253,6 +254,7 @@ shot_status build_grid(shot_plan_s* P, GridRec& g, int leg_mode, hipStream_t s) 
   // table rows padded to the matrix-core K step (32) for fp32/bf16 tables
   g.hpad = P->prec == SHOT_FP64 ? (g.h + 3) / 4 * 4 : (g.h + 31) / 32 * 32;
   g.fac = g.hp ? std::vector<int>() : fft_factors(d.nlon);
+  for (int r : fft_factors(d.nlon)) g.max_prime = std::max(g.max_prime, r == 4 ? 2 : r);
   if (!g.hp) {
     RingDev R{};
     const std::vector<int> f = fft_factors_wide(d.nlon), mg = fft_stage_magic(f);
@@ -737,7 +739,7 @@ RowArgs<T> row_args(const shot_plan_s* P, const GridRec& g, const Layout& Lo, co
   for (int i = 0; i < a.nfac && i < 8; ++i) a.fac[i] = g.fac[i];
   a.rowfft = g.d_rowfft;
   a.row_pad = g.hp ? g.d.nlon / 4 : g.row_pad;
-  a.max_prime = g.fac.empty() ? 0 : *std::max_element(g.fac.begin(), g.fac.end());
+  a.max_prime = g.max_prime;
   a.tw = static_cast<const cpx<T>*>(g.d_tw);
   a.aw = static_cast<const T*>(g.d_aw);
   if (g.hp) {

@@ -1110,16 +1110,23 @@ RowWaveShape row_wave_shape(const RowArgs<T>& a, int nb) {
     return w;
   }
   if (!a.ring && sizeof(T) == 4 && a.nlon == 1440) return w;  // row_sink_kernel, 512 lanes
+  // A belt of rings of 4 k p pixels, p a prime beyond 480 (one item: beyond 400): their
+  // radix-p stage takes (p - 1)^2 products a row pair, row_kernel's Bluestein transform
+  // two FFTs of 4096 points (a half at Nside 509: one item 229 us against 172, 4 items
+  // 655 against 610; Nside 449: one item 191 against 169, 4 items 437 against 529;
+  // Nside 401: one item 166.5 against 166.7).  Float64 rings that long have direct
+  // stages in either kernel.
+  if (a.ring && sizeof(T) == 4 && a.max_prime > (nb == 1 ? 400 : 480)) return w;
   // Run-time lengths: one wave per pair for rows of up to 200 points (192 points, one
   // item, a half: 9.7 us; float64 10.6 against 11.2 with 256 lanes), of up to 256 points
   // from 500 pairs on (240 points: one item 11.1 us against 10.2, 960 pairs reverse 14.7
   // against 18.0), with powers beyond 128 points from 640 pairs on (240 points, float64
   // half: one item 17.8 us against 13.2, 960 pairs 22.5 against 22.4); 256 lanes for
-  // longer rows (400 points: 15.1 against 11.9) and for large primes.  Rings from 512
-  // pairs on, where the launch fills the device (24 items at Nside 64: 23.9 against 37.4
-  // us; one item 16.6 against 11.9)
+  // longer rows (400 points: 15.1 against 11.9) and for large primes.  Rings of more than
+  // 128 pixels from 1200 pairs on (Nside 64, a half: 8 items 18.6 us against 16.6 with
+  // 256 lanes, 12 items 20.6 against 23.2).
   const int line = powers && a.nlon > 128 ? 640 : a.nlon > 200 ? 500 : 0;
-  const bool narrow = a.ring ? (a.nlon <= 128 || (a.nlon <= 256 && pairs >= 512))
+  const bool narrow = a.ring ? (a.nlon <= 128 || (a.nlon <= 256 && pairs >= 1200))
                              : a.max_prime <= 13 && a.nlon <= 256 && pairs >= line;
   w.tp = narrow ? 64 : 256;
   w.np = 1;

@@ -84,7 +84,7 @@ struct RowArgs {
   // rows (8s and 4s, then 2, 3, 5, other primes); LDS entries of a buffer
   const RingDev* rowfft;
   int wstride;
-  int max_prime;      // largest prime factor of a latitude-longitude grid's row length
+  int max_prime;      // largest prime factor of the row length (HEALPix: of the belt's rings)
   int row_pad;        // entries of padding that a run-time length's first stage writes
   const int* rpair;   // ring grids: ring pair run by workgroup column b (nullptr: xcd_row_pair order)
   cpx<T>* spec;

@@ -73,3 +73,12 @@ def test_balanced_and_unbalanced_on_one_plan():
         own = Plan([grid], precision="fp64", legendre="recurrence")
         a, b = one.sinkhorn(p, q, 0.5, tau, T=5), own.sinkhorn(p, q, 0.5, tau, T=5)
         assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1]) and a[2] == b[2]
+
+
+@pytest.mark.parametrize("grid,items,precision", [(("hp", 40, 40), 14, "fp32"), (("hp", 40, 40), 15, "fp32"),
+                                                  (("hp", 64, 60), 10, "fp64"), (("hp", 401, 20), 1, "fp32"),
+                                                  (("hp", 401, 20), 2, "fp32"), (("hp", 487, 20), 2, "fp32"),
+                                                  (("hp", 487, 20), 1, "fp64")])
+def test_rings(grid, items, precision):
+    """HEALPix below and from the pair count of whole waves a pair, and belts of long primes in both kernels."""
+    _check(grid, items, precision, taus=(math.inf, 1.0))
