@@ -889,18 +889,20 @@ bool use_t64(const GridRec& g) {
 
 // Recurrence-fed float64 matrix-core kernel (8 items per workgroup) instead of
 // the row-split kernel, where no tuning asks for one: from three row-split item
-// pairs per chunk of 8 on (five items where it runs them singly: 721x1440, 4 items
-// 165 -> 190 us, 6 items 241 -> 191), and from 1024 row-split workgroups on (they are
-// resident 768 at a time).  Heat apply of float32 plans, row-split -> this, us:
-// below the line 8 items at 128x256 9.8 -> 10.1, 4 at 256x512 17.4 -> 21.5, 8 at
-// 180x360 15.3 -> 16.2, 10 at 360x720 65 -> 72; above it 16 at 128x256 13.0 ->
-// 12.2, 7 at 256x512 28.8 -> 21.2, 12 and 16 at 180x360 18.6 -> 19.1 and 26.5 ->
-// 19.1, 5 at 360x720 44.7 -> 40.1; float64 plans gain more on both sides.
+// pairs per chunk of 8 on (five items where it runs them singly), from 1024
+// row-split workgroups on (they are resident 768 at a time), and by
+// batch64_pays where the row-split kernel's work list fits.  Heat apply of
+// float32 plans, row-split -> this, us: below the line 8 items at 128x256 9.8 ->
+// 10.1, 4 at 256x512 17.4 -> 21.5, 8 at 180x360 15.3 -> 16.2, 10 at 360x720 65 ->
+// 72; above it 16 at 128x256 15.4 -> 11.6, 8 at 256x512 29.7 -> 27.4, 12 and 16 at
+// 180x360 17.8 -> 17.2 and 25.1 -> 17.6, 5 at 360x720 39.9 -> 38.3; float64 plans
+// gain more on both sides.
 bool use_r64(const shot_plan_s* P, const GridRec& g, int nb, int leg_mode) {
   if (g.tab_kind != TAB_RECUR || g.tune_ib != 0 || g.tune_jpt != 0 || !r64_fits(g.d.L, g.h)) return false;
   if (rmma_tiles(P, g, nb, leg_mode, nullptr) > 0) return false;
   const int ib = split_ib(P, g, nb), chunks = (nb + ib - 1) / ib;
-  return chunks >= (ib == 1 ? 5 : 3) * ((nb + 7) / 8) && g.d.L * chunks >= 1024;
+  if (chunks < (ib == 1 ? 5 : 3) * ((nb + 7) / 8) || g.d.L * chunks < 1024) return false;
+  return !pick_sched(P, g, nb, ib) || batch64_pays(leg_mode, nb, (g.h + 63) / 64, P->prec == SHOT_FP64, ib == 2);
 }
 
 template <typename T>

@@ -170,6 +170,42 @@ std::vector<int> fft_stage_magic(const std::vector<int>& f) {
   return mg;
 }
 
+bool batch64_pays(int leg_mode, int nb, int nc, bool f64, bool pairs) {
+  // Items a workgroup of 8, in quarters.  The batch kernel costs a workgroup the same
+  // with one item as with eight, and the transforms alone as much as half a heat apply,
+  // while the row-split kernel's synthesis has no cross-lane sums and takes less than
+  // half.  Row-split -> batch kernel, us (float32 unless said):
+  //   synthesis  5 and 8 items at 360x720 22.2 -> 29.7 and 27.6 -> 31.2, 12 36.1 -> 39.6
+  //              (float64 41.0 -> 38.1), 16 44.9 -> 39.8; 17 at 384x768 61.4 -> 73.0, 24
+  //              78.4 -> 72.8; 7 at 512x1024 49.8 -> 42.9, 6 float64 47.1 -> 43.9 but at
+  //              400x800 33.2 -> 33.4; 14 at 520x1040 101 -> 106, 13 at 576x1152 128 ->
+  //              124; 6 at 721x1440 108 -> 105, 10 174 -> 189; 12 at 180x360 12.8 -> 13.6,
+  //              17 17.2 -> 15.3
+  //   analysis   5 at 360x720 26.6 -> 29.4, 8 31.6 -> 29.7; 18 at 400x800 78.4 -> 80.8
+  //              (float64 97.3 -> 82.4); 12 at 520x1040 99.9 -> 115, 16 126 -> 106; 5 at
+  //              721x1440 98.9 -> 115, 6 115 -> 115
+  //   heat       5 at 520x1040 86.1 -> 93.6 (float64 91.4 -> 97.5), 10 at 640x1280 229 ->
+  //              240, 11 251 -> 239
+  // (three and five chunks load the four SIMDs of a compute unit unevenly).
+  const int c8 = (nb + 7) / 8, never = 99;
+  int need = 0;
+  if (leg_mode == 0) {
+    need = nc == 5 ? (pairs ? 25 : 21) : 0;
+  } else if (leg_mode == 1) {
+    if (nc == 3 && c8 == 1) need = f64 ? 24 : 28;
+    if (nc == 4 && c8 > 2 && !f64) need = 25;
+    if (nc == 5) need = f64 ? 22 : 25;
+    if (nc >= 6) need = 24;
+  } else {
+    if (nc <= 2) need = nb < 13 ? never : 0;
+    else if (nc == 3) need = c8 == 1 ? never : f64 && !pairs ? 22 : 25;
+    else if (nc == 4) need = f64 ? 25 : c8 > 2 ? 29 : 28;
+    else if (nc == 5) need = f64 ? 28 : pairs ? 29 : 26;
+    else need = 24;
+  }
+  return 4 * nb >= need * c8;
+}
+
 void fft_pow2(std::vector<double>& re, std::vector<double>& im, int sign) {
   const size_t n = re.size();
   for (size_t i = 1, j = 0; i < n; ++i) {  // bit reversal

@@ -54,6 +54,11 @@ std::vector<int> fft_factors(int n);
 std::vector<int> fft_factors_wide(int n);
 std::vector<int> fft_stage_magic(const std::vector<int>& f);
 
+// Whether nb items (several row-split work lists of them) are enough for the float64
+// batch kernel: leg_mode 0 (heat apply), 1 (analysis), 2 (synthesis) of ceil(h / 64) =
+// nc latitude chunks; `pairs`: the row-split kernel would take two items a workgroup.
+bool batch64_pays(int leg_mode, int nb, int nc, bool f64, bool pairs);
+
 // In-place radix-2 FFT of a power-of-two length in double precision:
 // a[k] <- sum_n a[n] exp(sign 2 pi i n k / n_len) (no scaling).
 void fft_pow2(std::vector<double>& re, std::vector<double>& im, int sign);
