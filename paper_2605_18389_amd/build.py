@@ -32,8 +32,8 @@ SOURCES = [
 ]
 
 
-HASHED = ["api.cpp", "host_math.cpp", "host_math.h", "shot_internal.h", "device_common.h", "kernels.hip",
-          "rows_wave.hip", "legendre64.hip"]
+HASHED = ["api.cpp", "host_math.cpp", "host_math.h", "shot_internal.h", "device_common.h", "launch.h",
+          "per_device.h", "kernels.hip", "rows_wave.hip", "legendre64.hip"]
 
 
 def source_hash():

@@ -30,6 +30,7 @@
 
 #include "device_common.h"
 #include "host_math.h"
+#include "launch.h"
 #include "shot_internal.h"
 
 namespace shot {
@@ -2773,15 +2774,9 @@ static hipError_t launch_rows_nc(const RowArgs<T>& a, int nb, hipStream_t stream
   // to 96 KiB for 2048-point fp64 rows and 160 KiB for rings
   const size_t nbuf = a.ring ? (size_t)a.nbuf : (size_t)a.nlon;
   const size_t lds = (size_t)(2 * RPW + 1) * nbuf * sizeof(cpx<T>);
-  if (lds > 65536) {
-    static size_t attr_bytes = 65536;  // dynamic LDS enabled so far, per kernel instantiation
-    if (lds > attr_bytes) {
-      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&row_kernel<T, RPW, NC, BS>),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      if (e != hipSuccess) return e;
-      attr_bytes = lds;
-    }
-  }
+  static std::atomic<unsigned long long> lds_set{0};
+  hipError_t e = allow_lds(reinterpret_cast<const void*>(&row_kernel<T, RPW, NC, BS>), lds, lds_set);
+  if (e != hipSuccess) return e;
   SHOT_LAUNCH((row_kernel<T, RPW, NC, BS>), grid, dim3(BS), lds, stream, b);
   return hipGetLastError();
 }
@@ -2953,15 +2948,10 @@ static hipError_t launch_mma_nt(const LegArgs<T>& a, hipStream_t stream) {
   // orders) or several column tiles it measured slower, so those run m = b.
   LegArgs<T> b = a;
   if (grid.y > 1 || lds > 160 * 1024 / 3) b.morder = nullptr;
-  if (lds > 65536) {  // long orders of fp32 tables: one workgroup per compute unit
-    static size_t attr_bytes = 65536;  // dynamic LDS enabled so far for this instantiation
-    if (lds > attr_bytes) {
-      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&legendre_mma_kernel<T, TT, NT, NARROW, NW>),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      if (e != hipSuccess) return e;
-      attr_bytes = lds;
-    }
-  }
+  // (beyond 64 KiB: long orders of fp32 tables, one workgroup per compute unit)
+  static std::atomic<unsigned long long> lds_set{0};
+  hipError_t e = allow_lds(reinterpret_cast<const void*>(&legendre_mma_kernel<T, TT, NT, NARROW, NW>), lds, lds_set);
+  if (e != hipSuccess) return e;
   SHOT_LAUNCH((legendre_mma_kernel<T, TT, NT, NARROW, NW>), grid, dim3(64 * NW), lds, stream, b);
   return hipGetLastError();
 }
@@ -3031,15 +3021,10 @@ static hipError_t launch_rmma_nt(const LegArgs<T>& a, hipStream_t stream) {
     const int nw = (a.h + 63) / 64;
     const RmLayout Q = rm_layout(a.L, a.h, NT, nw, TR::ES, TR::PLANES);
     if (nw > 8 || Q.total > 160 * 1024) return hipErrorInvalidValue;
-    if (Q.total > 65536) {
-      static size_t attr_bytes = 65536;  // dynamic LDS enabled so far for this instantiation
-      if (Q.total > attr_bytes) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&legendre_rmma_kernel<T, OP, NT, SRC, MODE, WPE>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)Q.total);
-        if (e != hipSuccess) return e;
-        attr_bytes = Q.total;
-      }
-    }
+    static std::atomic<unsigned long long> lds_set{0};
+    hipError_t e = allow_lds(reinterpret_cast<const void*>(&legendre_rmma_kernel<T, OP, NT, SRC, MODE, WPE>), Q.total,
+                             lds_set);
+    if (e != hipSuccess) return e;
     dim3 grid(a.L, (2 * a.nb + Q.ncol - 1) / Q.ncol);
     SHOT_LAUNCH((legendre_rmma_kernel<T, OP, NT, SRC, MODE, WPE>), grid, dim3(64 * nw), Q.total, stream, a);
     return hipGetLastError();

@@ -21,6 +21,7 @@
 #include <hip/hip_ext.h>
 
 #include "device_common.h"
+#include "launch.h"
 
 namespace shot {
 
@@ -202,15 +203,9 @@ template <int MODE, int BT>
 hipError_t launch_mode(const LegArgs<double>& a, hipStream_t stream) {
   const int nc = (a.h + 63) / 64;
   const size_t lds = t64_layout(nc).total;
-  if (lds > 65536) {
-    static size_t enabled = 65536;
-    if (lds > enabled) {
-      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&legendre_t64_kernel<MODE, BT>),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      if (e != hipSuccess) return e;
-      enabled = lds;
-    }
-  }
+  static std::atomic<unsigned long long> lds_set{0};
+  hipError_t e = allow_lds(reinterpret_cast<const void*>(&legendre_t64_kernel<MODE, BT>), lds, lds_set);
+  if (e != hipSuccess) return e;
   dim3 grid(a.L, (a.nb + 7) / 8);
   hipEvent_t e0, e1;
   if (take_launch_events(&e0, &e1))
@@ -473,15 +468,9 @@ template <typename T, int MODE, int BT>
 hipError_t launch_r64_mode(const LegArgs<T>& a, hipStream_t stream) {
   const int nc = (a.h + 63) / 64;
   const size_t lds = r64_layout(a.L, nc).total;
-  if (lds > 65536) {
-    static size_t enabled = 65536;
-    if (lds > enabled) {
-      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&legendre_r64_kernel<T, MODE, BT>),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      if (e != hipSuccess) return e;
-      enabled = lds;
-    }
-  }
+  static std::atomic<unsigned long long> lds_set{0};
+  hipError_t e = allow_lds(reinterpret_cast<const void*>(&legendre_r64_kernel<T, MODE, BT>), lds, lds_set);
+  if (e != hipSuccess) return e;
   dim3 grid(a.L, (a.nb + 7) / 8);
   hipEvent_t e0, e1;
   if (take_launch_events(&e0, &e1))

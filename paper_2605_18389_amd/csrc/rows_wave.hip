@@ -32,6 +32,7 @@
 #include <hip/hip_ext.h>
 
 #include "device_common.h"
+#include "launch.h"
 
 namespace shot {
 
@@ -1000,16 +1001,6 @@ static int wave_stride_rt(int nbuf, int pad, int need) {
     else hipLaunchKernelGGL(kernel, grid, block, lds, stream, arg);                                     \
   } while (0)
 
-// Dynamic LDS beyond 64 KiB has to be enabled once per kernel (the largest size asked for so far).
-template <typename K>
-static hipError_t allow_lds(K kernel, size_t lds, size_t& enabled) {
-  if (lds <= enabled) return hipSuccess;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     (int)lds);
-  if (e == hipSuccess) enabled = lds;
-  return e;
-}
-
 template <typename T, int NC, int TP, int NPC, int KIND>
 static hipError_t launch_ct(RowArgs<T> a, int nb, int mod, hipStream_t stream) {
   using F = RowFac<NC, TP>;
@@ -1017,8 +1008,8 @@ static hipError_t launch_ct(RowArgs<T> a, int nb, int mod, hipStream_t stream) {
   const int pf = F::r[0] % 2 == 0 ? NC / F::r[0] : 0, pi = F::r[F::n - 1] % 2 == 0 ? NC / F::r[F::n - 1] : 0;
   a.wstride = wave_stride_ct(NC, std::max(pf, pi), mod);
   const size_t lds = ((size_t)NPC * a.wstride + NC) * sizeof(cpx<T>);
-  static size_t enabled = 65536;
-  hipError_t e = allow_lds(&row_wave_kernel<T, NC, TP, NPC, KIND>, lds, enabled);
+  static std::atomic<unsigned long long> lds_set{0};
+  hipError_t e = allow_lds(reinterpret_cast<const void*>(&row_wave_kernel<T, NC, TP, NPC, KIND>), lds, lds_set);
   if (e != hipSuccess) return e;
   dim3 grid((a.h + NPC - 1) / NPC, nb);
   ROWW_LAUNCH((row_wave_kernel<T, NC, TP, NPC, KIND>), grid, dim3(TP * NPC), lds, stream, a);
@@ -1029,8 +1020,8 @@ template <typename T, int TP, int KIND>
 static hipError_t launch_rt(RowArgs<T> a, int nb, int np, hipStream_t stream) {
   a.wstride = wave_stride_rt(a.nlon, a.row_pad, std::max(a.ring ? 2 * a.L : 0, TP));
   const size_t lds = ((size_t)np * 2 * a.wstride + (size_t)(a.ring ? np : 1) * a.nlon) * sizeof(cpx<T>);
-  static size_t enabled = 65536;
-  hipError_t e = allow_lds(&row_wave_kernel<T, 0, TP, 1, KIND>, lds, enabled);
+  static std::atomic<unsigned long long> lds_set{0};
+  hipError_t e = allow_lds(reinterpret_cast<const void*>(&row_wave_kernel<T, 0, TP, 1, KIND>), lds, lds_set);
   if (e != hipSuccess) return e;
   dim3 grid((a.h + np - 1) / np, nb);
   ROWW_LAUNCH((row_wave_kernel<T, 0, TP, 1, KIND>), grid, dim3(TP * np), lds, stream, a);
