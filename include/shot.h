@@ -256,14 +256,14 @@ shot_status shot_gradient_regional_rms(shot_plan_t plan, const int32_t* grid_of_
  * bfloat16 plans always use) and, as the second value, for SHOT_LEG_RECURRENCE grids the latitude chains
  * per thread of the latitude-split kernel (1, 2 or 4, at most 256 threads per
  * workgroup; 0 = the row-split kernel, and with both values 0 float64 matrix
- * cores for batches of grids of at most 768 rows), for SHOT_LEG_TABLE grids of float32 and
+ * cores for batches of grids of at most 640 rows, or 768 with L <= 800), for SHOT_LEG_TABLE grids of float32 and
  * bfloat16 plans the matrix-core kernel's column tiles per workgroup (1, 2 or 4
  * tiles of 16 columns = 8, 16 or 32 items; float32 grids of at most 1024 rows
  * always take 8; 0 = automatic: matrix cores for any
  * number of items, 1 tile below 16 items, 2 from 16, 4 from 32, fewer while
  * they overflow 60 KiB of LDS; -1 = VALU kernel only; a table whose single
  * tile would need more than 150 KiB of LDS runs the VALU kernel).  float64
- * tables of at most 1024 rows run their matrix-core kernel with both values 0,
+ * tables of at most 896 rows run their matrix-core kernel with both values 0,
  * the VALU kernel otherwise.
  * SHOT_E_INVALID otherwise. */
 shot_status shot_plan_set_tuning(shot_plan_t plan, int32_t grid, int32_t items_per_block,

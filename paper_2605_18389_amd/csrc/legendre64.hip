@@ -68,7 +68,7 @@ __device__ __forceinline__ void lanegroup_transpose4d(double* r) {
     r[e] = __longlong_as_double((long long)((unsigned long long)lo[e] | ((unsigned long long)hi[e] << 32)));
 }
 
-template <int MODE, int BT>  // BT: 768 threads (168 registers) up to 384 latitude pairs, 1024 beyond
+template <int MODE, int BT>  // BT: 768 threads (168 registers) up to 384 latitude pairs, 1024 up to 448
 __global__ void __launch_bounds__(BT) legendre_t64_kernel(LegArgs<double> A) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int L = A.L, h = A.h, hpad = A.hpad;
@@ -491,7 +491,7 @@ hipError_t launch_r64_bt(const LegArgs<T>& a, hipStream_t stream) {
 
 }  // namespace
 
-bool t64_fits(int h) { return h <= 512 && t64_layout((h + 63) / 64).total <= 160 * 1024; }
+bool t64_fits(int h) { return t64_layout((h + 63) / 64).total <= 160 * 1024; }  // h <= 448
 
 hipError_t launch_legendre_t64(const LegArgs<double>& a, hipStream_t stream) {
   if (!t64_fits(a.h)) return hipErrorInvalidValue;

@@ -221,7 +221,8 @@ template <typename T>
 hipError_t launch_legendre_mma(const LegArgs<T>& a, int table_kind, int nt, hipStream_t stream);
 size_t mma_lds_bytes(int L, int hpad, int nt, int table_kind, bool narrow = false);
 
-// Matrix-core kernel of float64 tables (legendre64.hip), at most 512 latitude pairs.
+// Matrix-core kernel of float64 tables (legendre64.hip): at most 448 latitude pairs,
+// whose seven chunks fill the LDS (162 816 of 163 840 bytes).
 bool t64_fits(int h);
 hipError_t launch_legendre_t64(const LegArgs<double>& a, hipStream_t stream);
 // Its recurrence-fed form.

@@ -31,3 +31,17 @@ def test_batch_kernel_line(lib, mode, items, h, f64, pairs, batch):
     f.argtypes = [ctypes.c_int] * 3 + [ctypes.c_bool] * 2
     f.restype = ctypes.c_bool
     assert f(mode, items, (h + 63) // 64, bool(f64), bool(pairs)) == bool(batch)
+
+
+def test_limits_of_the_float64_kernels(lib):
+    """The sizes that include/shot.h states: tables of 896 rows; recurrence batches of 640 rows, or 768 up to L = 800."""
+    t, r = lib._ZN4shot8t64_fitsEi, lib._ZN4shot8r64_fitsEii
+    t.argtypes, r.argtypes = [ctypes.c_int], [ctypes.c_int] * 2
+    t.restype = r.restype = ctypes.c_bool
+    assert [h for h in range(1, 1025) if t(h)] == list(range(1, 449))
+    assert all(r(1024, h) for h in range(1, 321))
+    assert all(r(800, h) and not r(801, h) for h in range(321, 385))
+    assert not any(r(1, h) for h in range(385, 1025))
+    text = open(os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "include", "shot.h")).read()
+    text = " ".join(text.replace("*", " ").split())
+    assert "float64 tables of at most 896 rows" in text and "at most 640 rows, or 768 with L <= 800" in text
