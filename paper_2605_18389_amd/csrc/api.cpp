@@ -833,6 +833,12 @@ bool use_split(const shot_plan_s* P, const GridRec& g) {
   return pick_sched(P, g, 1, 1) != nullptr;
 }
 
+// Float32 tables of up to 512 latitude pairs run the single-pass kernel, 8 items per
+// workgroup whatever the tuned tile count.
+bool one_pass_table(const GridRec& g) {
+  return g.tab_kind == TAB_F32 && g.h <= 512 && rmma_lds_bytes(g.d.L, g.h, 1, RM_F32) <= 160 * 1024;
+}
+
 // Matrix-core kernel for table grids: column tiles per workgroup, or 0 for
 // the VALU kernels.  Automatic: matrix cores from 4 items on, the widest tile
 // count (<= the batch) whose LDS staging fits.
@@ -842,10 +848,7 @@ int mma_tiles(const shot_plan_s* P, const GridRec& g, int count) {
   // Matrix cores for any item count: they stream the table faster than the
   // VALU table kernel even for a single item (one item at L = 720: bf16
   // 0.58 -> 0.12 ms per launch, fp32 0.80 -> 0.53 ms)
-  // float32 tables of up to 512 latitude pairs run the single-pass kernel (8
-  // items per workgroup whatever the tuned tile count)
-  if (g.tab_kind == TAB_F32 && g.h <= 512 && rmma_lds_bytes(g.d.L, g.h, 1, RM_F32) <= 160 * 1024)
-    return nt > 0 ? nt : 1;
+  if (one_pass_table(g)) return nt > 0 ? nt : 1;
   if (nt == 0) nt = count >= 32 ? 4 : (count >= 16 ? 2 : 1);
   // fewer column tiles while they overflow 60 KiB of LDS (several workgroups
   // per compute unit); one tile may take up to 150 KiB (fp32 tables of long
@@ -1361,7 +1364,7 @@ shot_status autotune_impl(shot_plan_s* P, GridRec& g, const Layout& Lo, int nite
   if (g.tab_kind == TAB_RECUR || (g.tab_kind == TAB_F64 && t64_fits(g.h))) cand.push_back({0, 0});  // float64 matrix cores
   if (mma_table(g))
     for (int nt : {1, 2, 4})
-      if (16 * nt <= 2 * std::max(nitems, 8)) cand.push_back({0, nt});
+      if (nt == 1 || (16 * nt <= 2 * std::max(nitems, 8) && !one_pass_table(g))) cand.push_back({0, nt});
   if (g.tab_kind == TAB_RECUR && P->prec != SHOT_FP64) {
     // bfloat16 and split-bfloat16 plans compute on matrix cores only
     if (P->prec != SHOT_FP32) cand.clear();
