@@ -119,18 +119,14 @@ __device__ __forceinline__ void butterfly(cpx<T>* v, T s) {
 
 template <typename T, int R>
 __device__ __forceinline__ void stockham_stage(const cpx<T>* __restrict__ src, cpx<T>* __restrict__ dst,
-                                               int N, int Ns, int nb, const cpx<T>* __restrict__ tw, T sign) {
-  // nb independent transforms of length N stored back to back
+                                               int N, int Ns, const cpx<T>* __restrict__ tw, T sign) {
   const int NR = N / R;
   const int twstride = N / (Ns * R);
-  for (int bb = threadIdx.x; bb < nb * NR; bb += blockDim.x) {
-    const int t = bb / NR, b = bb - t * NR;
-    const cpx<T>* s = src + t * N;
-    cpx<T>* d = dst + t * N;
+  for (int b = threadIdx.x; b < NR; b += blockDim.x) {
     const int k = b % Ns;
     cpx<T> v[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) v[r] = s[b + r * NR];
+    for (int r = 0; r < R; ++r) v[r] = src[b + r * NR];
 #pragma unroll
     for (int r = 1; r < R; ++r) {
       cpx<T> w = tw[r * k * twstride];
@@ -140,7 +136,7 @@ __device__ __forceinline__ void stockham_stage(const cpx<T>* __restrict__ src, c
     butterfly<T, R>(v, sign);
     const int base = (b / Ns) * Ns * R + k;
 #pragma unroll
-    for (int r = 0; r < R; ++r) d[base + r * Ns] = v[r];
+    for (int r = 0; r < R; ++r) dst[base + r * Ns] = v[r];
   }
 }
 
@@ -150,14 +146,12 @@ __device__ __forceinline__ void stockham_stage(const cpx<T>* __restrict__ src, c
 // root, so every term costs one table lookup.
 template <typename T>
 __device__ __forceinline__ void stockham_stage_generic(const cpx<T>* __restrict__ src, cpx<T>* __restrict__ dst, int N, int Ns,
-                                       int R, int nb, const cpx<T>* __restrict__ tw, T sign) {
+                                       int R, const cpx<T>* __restrict__ tw, T sign) {
   const int NR = N / R;
   const int twstride = N / (Ns * R);
-  for (int o = threadIdx.x; o < nb * N; o += blockDim.x) {
-    const int t = o / N, rem = o - t * N;
-    const int q = rem / NR, b = rem - q * NR;
+  for (int o = threadIdx.x; o < N; o += blockDim.x) {
+    const int q = o / NR, b = o - q * NR;
     const int k = b % Ns;
-    const cpx<T>* s = src + t * N;
     const int e = k * twstride + q * NR;
     cpx<T> acc = {(T)0, (T)0};
     int idx = 0;  // r * e mod N, advanced by e (< N, so one subtraction wraps it)
@@ -174,7 +168,7 @@ __device__ __forceinline__ void stockham_stage_generic(const cpx<T>* __restrict_
       }
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        v[j] = s[b + (r + j) * NR];
+        v[j] = src[b + (r + j) * NR];
         w[j] = tw[ix[j]];
       }
 #pragma unroll
@@ -186,16 +180,16 @@ __device__ __forceinline__ void stockham_stage_generic(const cpx<T>* __restrict_
     for (; r < R; ++r) {
       cpx<T> w = tw[idx];
       w.y *= -sign;
-      acc = cadd(acc, cmul(s[b + r * NR], w));
+      acc = cadd(acc, cmul(src[b + r * NR], w));
       idx += e;
       idx = idx >= N ? idx - N : idx;
     }
-    dst[t * N + (b / Ns) * Ns * R + k + q * Ns] = acc;
+    dst[(b / Ns) * Ns * R + k + q * Ns] = acc;
   }
 }
 
 template <typename T>
-__device__ __forceinline__ cpx<T>* fft_lds(cpx<T>* a, cpx<T>* b, int N, int nb, const int* fac, int nfac,
+__device__ __forceinline__ cpx<T>* fft_lds(cpx<T>* a, cpx<T>* b, int N, const int* fac, int nfac,
                            const cpx<T>* __restrict__ tw, T sign) {
   int Ns = 1;
   cpx<T>* src = a;
@@ -203,11 +197,11 @@ __device__ __forceinline__ cpx<T>* fft_lds(cpx<T>* a, cpx<T>* b, int N, int nb, 
   for (int s = 0; s < nfac; ++s) {
     const int R = fac[s];
     switch (R) {
-      case 2: stockham_stage<T, 2>(src, dst, N, Ns, nb, tw, sign); break;
-      case 3: stockham_stage<T, 3>(src, dst, N, Ns, nb, tw, sign); break;
-      case 4: stockham_stage<T, 4>(src, dst, N, Ns, nb, tw, sign); break;
-      case 5: stockham_stage<T, 5>(src, dst, N, Ns, nb, tw, sign); break;
-      default: stockham_stage_generic<T>(src, dst, N, Ns, R, nb, tw, sign); break;
+      case 2: stockham_stage<T, 2>(src, dst, N, Ns, tw, sign); break;
+      case 3: stockham_stage<T, 3>(src, dst, N, Ns, tw, sign); break;
+      case 4: stockham_stage<T, 4>(src, dst, N, Ns, tw, sign); break;
+      case 5: stockham_stage<T, 5>(src, dst, N, Ns, tw, sign); break;
+      default: stockham_stage_generic<T>(src, dst, N, Ns, R, tw, sign); break;
     }
     __syncthreads();
     cpx<T>* t = src;
@@ -264,19 +258,16 @@ __host__ __device__ constexpr int fac_prefix(FacList f, int s) {
   return p;
 }
 
-template <typename T, int R, int N, int Ns, int NB>
+template <typename T, int R, int N, int Ns>
 __device__ __forceinline__ void stockham_stage_c(const cpx<T>* __restrict__ src, cpx<T>* __restrict__ dst,
                                                  const cpx<T>* __restrict__ tw, T sign) {
   constexpr int NR = N / R;
   constexpr int twstride = N / (Ns * R);
-  for (int bb = threadIdx.x; bb < NB * NR; bb += blockDim.x) {
-    const int t = bb / NR, b = bb - t * NR;
-    const cpx<T>* s = src + t * N;
-    cpx<T>* d = dst + t * N;
+  for (int b = threadIdx.x; b < NR; b += blockDim.x) {
     const int k = b % Ns;
     cpx<T> v[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) v[r] = s[b + r * NR];
+    for (int r = 0; r < R; ++r) v[r] = src[b + r * NR];
 #pragma unroll
     for (int r = 1; r < R; ++r) {
       cpx<T> w = tw[r * k * twstride];
@@ -286,36 +277,36 @@ __device__ __forceinline__ void stockham_stage_c(const cpx<T>* __restrict__ src,
     butterfly<T, R>(v, sign);
     const int base = (b / Ns) * Ns * R + k;
 #pragma unroll
-    for (int r = 0; r < R; ++r) d[base + r * Ns] = v[r];
+    for (int r = 0; r < R; ++r) dst[base + r * Ns] = v[r];
   }
 }
 
-template <typename T, int N, int NB, int S>
+template <typename T, int N, int S>
 __device__ __forceinline__ void fft_stages_c(cpx<T>*& src, cpx<T>*& dst, const cpx<T>* tw, T sign) {
   constexpr FacList F = fuse_factors(factorize(N));
   if constexpr (S < F.n) {
     constexpr int R = F.r[S];
     constexpr int Ns = fac_prefix(F, S);
-    stockham_stage_c<T, R, N, Ns, NB>(src, dst, tw, sign);
+    stockham_stage_c<T, R, N, Ns>(src, dst, tw, sign);
     __syncthreads();
     cpx<T>* t = src;
     src = dst;
     dst = t;
-    fft_stages_c<T, N, NB, S + 1>(src, dst, tw, sign);
+    fft_stages_c<T, N, S + 1>(src, dst, tw, sign);
   }
 }
 
 // Length chosen at compile time (NC > 0) or at run time (NC == 0).
-template <typename T, int NC, int NB>
+template <typename T, int NC>
 __device__ __forceinline__ cpx<T>* fft_any(cpx<T>* a, cpx<T>* b, int N, const int* fac, int nfac,
                                            const cpx<T>* tw, T sign) {
   if constexpr (NC > 0) {
     cpx<T>* src = a;
     cpx<T>* dst = b;
-    fft_stages_c<T, NC, NB, 0>(src, dst, tw, sign);
+    fft_stages_c<T, NC, 0>(src, dst, tw, sign);
     return src;
   } else {
-    return fft_lds<T>(a, b, N, NB, fac, nfac, tw, sign);
+    return fft_lds<T>(a, b, N, fac, nfac, tw, sign);
   }
 }
 
@@ -633,6 +624,14 @@ __device__ void kratio_fold(const RowArgs<T>& A, int it, int k, int slot, double
     const double r = (mx > 0.0 && isfinite(mn)) ? mn / mx : -INFINITY;
     A.kr[it] = fmin(A.kr[it], r);
   }
+}
+
+// Orders the lanes of a wave through LDS: its LDS operations complete in order, so
+// only the compiler has to keep them in place.
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Row (m, l = m) of the packed (m, l) triangle.

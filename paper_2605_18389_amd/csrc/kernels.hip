@@ -26,8 +26,6 @@
 #include <cfloat>
 #include <climits>
 
-#include <hip/hip_ext.h>
-
 #include "device_common.h"
 #include "host_math.h"
 #include "launch.h"
@@ -36,13 +34,9 @@
 namespace shot {
 
 // ---------------------------------------------------------------------------
-// Row kernel: the modes and sizes that row_wave_kernel does not run.  grid =
-// (ceil(h / RPW) groups of RPW row pairs, items; RPW = 1 in every launch), block 256.
-// Each row pair (j, nlat-1-j) rides in one complex FFT; the RPW pairs of a
-// group share the twiddles and the barriers of the staged FFTs, and their
-// spectral entries (m, j..j+RPW-1) are contiguous in memory.  Per-row-pair
-// partial sums are written at the group's first pair (the other slots of the
-// group get the neutral element) so all consumers still reduce over j < h.
+// Row kernel: the modes and sizes that row_wave_kernel does not run.  grid = (h
+// row pairs, items), BS threads.  Each row pair (j, nlat-1-j) rides in one complex
+// FFT, whose stages the workgroup's threads share.
 // ---------------------------------------------------------------------------
 // Transform of one ring pair's packed row (length n = RG->len), in LDS
 // buffers a and b of at least max(n, RG->bm) entries; returns the buffer
@@ -73,7 +67,7 @@ __device__ __forceinline__ cpx<T>* ring_fft(cpx<T>* a, cpx<T>* b, int n, const R
   cpx<T>* y = a;
   for (int pass = 0; pass < (bs ? 2 : 1); ++pass) {
     const T sg = bs ? (pass ? (T)1 : (T)-1) : sign;
-    y = fft_lds<T>(y, y == a ? b : a, bs ? M : n, 1, bs ? RG->bm_fac : RG->fac, bs ? RG->bm_nfac : RG->nfac, tw,
+    y = fft_lds<T>(y, y == a ? b : a, bs ? M : n, bs ? RG->bm_fac : RG->fac, bs ? RG->bm_nfac : RG->nfac, tw,
                    sg);
     if (bs && pass == 0) {
       for (int k = threadIdx.x; k < M; k += blockDim.x) {
@@ -103,27 +97,24 @@ __device__ __forceinline__ T pick2(const T (&a)[2][2], int e, int r) {
   return e ? y : x;
 }
 
-template <typename T, int RPW, int NC, int BS = 256>
+template <typename T, int NC, int BS = 256>
 __global__ void __launch_bounds__(BS) row_kernel(RowArgs<T> A) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int L = A.L, h = A.h;
   // Workgroups are dealt round-robin to the 8 XCDs; give each XCD a
-  // contiguous range of groups so that neighbouring rows' spectral entries
+  // contiguous range of pairs so that neighbouring rows' spectral entries
   // (adjacent in memory) meet in the same L2.
-  const int ngroups = (h + RPW - 1) / RPW;
-  const int jp0 = (A.rpair ? A.rpair[blockIdx.x] : xcd_row_pair(blockIdx.x, ngroups)) * RPW;
-  // HEALPix: this pair's rings (one pair per group), else uniform rows
-  const RingDev* RG = A.ring ? A.ring + jp0 : nullptr;
+  const int jp = A.rpair ? A.rpair[blockIdx.x] : xcd_row_pair(blockIdx.x, h);
+  // HEALPix: this pair's rings, else uniform rows
+  const RingDev* RG = A.ring ? A.ring + jp : nullptr;
   const int N = RG ? RG->len : (NC > 0 ? NC : A.nlon);
   const int NB = RG ? A.nbuf : N;  // LDS stride: the longest ring or Bluestein convolution
   cpx<T>* buf0 = reinterpret_cast<cpx<T>*>(smem_raw);
-  cpx<T>* buf1 = buf0 + RPW * NB;
-  cpx<T>* twl = buf1 + RPW * NB;
+  cpx<T>* buf1 = buf0 + NB;
+  cpx<T>* twl = buf1 + NB;
   __shared__ double sh[16];
   __shared__ int sh_bad;
-  __shared__ T awl[RPW];
 
-  const int np = min(RPW, h - jp0);  // active pairs of this group
   const int it = A.item0 + blockIdx.y;
   const ItemDev I = A.items[it];
   const int nlat = A.nlat;
@@ -135,7 +126,11 @@ __global__ void __launch_bounds__(BS) row_kernel(RowArgs<T> A) {
   using GT = const __attribute__((address_space(1))) T;
   GT* P = (GT*)static_cast<const T*>(I.p);
   GT* Q = (GT*)static_cast<const T*>(I.q);
-  if (tid < RPW) awl[tid] = (tid < np) ? A.aw[jp0 + tid] : (T)0;
+  const int j2 = nlat - 1 - jp;
+  const bool eq = (jp == j2);  // the equator row of an odd grid
+  const long long r1 = I.foff + (RG ? (long long)RG->off1 : (long long)jp * N);
+  const long long r2 = I.foff + (RG ? (long long)RG->off2 : (long long)j2 * N);
+  const T aj = A.aw[jp];
   if (tid == 0) sh_bad = 0;
 
   double g = 1.0;
@@ -144,23 +139,12 @@ __global__ void __launch_bounds__(BS) row_kernel(RowArgs<T> A) {
   else if (mode == ROW_SINK_U && A.k > 1) g = gauge(A, I, it, A.k - 1, sh);
   __syncthreads();
 
-// per-element pair geometry: pr = pair in group, c = column
-#define ROW_PAIR_SETUP(idx)                                                        \
-  const int pr = (idx) / N, c = (idx) - pr * N;                                    \
-  const int jp = jp0 + pr;                                                         \
-  const int j2 = nlat - 1 - jp;                                                    \
-  const bool eq = (jp == j2);                                                      \
-  const long long r1 = I.foff + (RG ? (long long)RG->off1 : (long long)jp * N);    \
-  const long long r2 = I.foff + (RG ? (long long)RG->off2 : (long long)j2 * N);    \
-  const T aj = awl[pr];
-
   if (mode == ROW_FINAL) {
     const T* uh = ubuf_of(A, A.k) + I.foff;
     const T* vh = vbuf_of(A, A.k) + I.foff;
     const double lg = log(g);
     double acc = 0.0;
-    for (int idx = tid; idx < np * N; idx += bs) {
-      ROW_PAIR_SETUP(idx)
+    for (int c = tid; c < N; c += bs) {
       for (int rr = 0; rr < (eq ? 1 : 2); ++rr) {
         const long long fidx = (rr ? r2 : r1) + c;
         const long long fi = fidx - I.foff;
@@ -175,7 +159,7 @@ __global__ void __launch_bounds__(BS) row_kernel(RowArgs<T> A) {
       }
     }
     acc = block_sum(acc, sh);
-    if (tid < np) A.prep[((size_t)it * A.hs + jp0 + tid) * 4 + 3] = (tid == 0) ? acc : 0.0;
+    if (tid == 0) A.prep[((size_t)it * A.hs + jp) * 4 + 3] = acc;
     if (A.kr && blockIdx.x == 0 && A.k >= 1) kratio_fold(A, it, A.k, 4, sh);
     return;
   }
@@ -196,7 +180,7 @@ __global__ void __launch_bounds__(BS) row_kernel(RowArgs<T> A) {
   // their latency hides behind the inverse FFT (up to PF columns per thread)
   constexpr int PF = 2;
   const bool sink = (mode == ROW_SINK_U || mode == ROW_SINK_V || mode == ROW_CHECK);
-  const bool pre = sink && np * N <= PF * bs;
+  const bool pre = sink && N <= PF * bs;
   const bool chk_u = (mode == ROW_SINK_U || mode == ROW_CHECK) && A.chk_slot >= 0;
   T pfv[PF][2], pfu[PF][2];
   if (pre) {
@@ -204,10 +188,7 @@ __global__ void __launch_bounds__(BS) row_kernel(RowArgs<T> A) {
     const T* uo = ubuf_of(A, A.k - 1);
 #pragma unroll
     for (int e = 0; e < PF; ++e) {
-      const int idx = min(tid + e * bs, np * N - 1);
-      ROW_PAIR_SETUP(idx)
-      (void)eq;
-      (void)aj;
+      const int c = min(tid + e * bs, N - 1);
       pfv[e][0] = Fm[r1 + c];
       pfv[e][1] = Fm[r2 + c];
       pfu[e][0] = pfu[e][1] = (T)0;
@@ -225,15 +206,14 @@ __global__ void __launch_bounds__(BS) row_kernel(RowArgs<T> A) {
     // Short rings collect many orders per bin: G threads share a bin (orders
     // split by stride G N) and their partials are added in a fixed order.
     __shared__ cpx<T> ringpart[BS];
-    const cpx<T>* ph = A.ring_ph + (size_t)jp0 * L;
-    const bool eq = (jp0 == nlat - 1 - jp0);
+    const cpx<T>* ph = A.ring_ph + (size_t)jp * L;
     const int G = N >= bs ? 1 : bs / N;  // N * G <= bs = BS
     for (int t = tid; t < N * G; t += bs) {
       const int c = t % N, g = t / N;
       cpx<T> z = {(T)0, (T)0};
       for (int m = c + g * N; m < L; m += G * N) {
         cpx<T> ge, go;
-        load_spec_pair(A, spec, it, m, jp0, ge, go);
+        load_spec_pair(A, spec, it, m, jp, ge, go);
         const cpx<T> a = cmul(cadd(ge, go), ph[m]);
         const cpx<T> b = eq ? cpx<T>{(T)0, (T)0} : cmul(csub(ge, go), ph[m]);
         z.x += a.x - b.y;
@@ -241,7 +221,7 @@ __global__ void __launch_bounds__(BS) row_kernel(RowArgs<T> A) {
       }
       for (int m = (c == 0 ? N : N - c) + g * N; m < L; m += G * N) {
         cpx<T> ge, go;
-        load_spec_pair(A, spec, it, m, jp0, ge, go);
+        load_spec_pair(A, spec, it, m, jp, ge, go);
         const cpx<T> a = cmul(cadd(ge, go), ph[m]);
         const cpx<T> b = eq ? cpx<T>{(T)0, (T)0} : cmul(csub(ge, go), ph[m]);
         z.x += a.x + b.y;
@@ -263,32 +243,25 @@ __global__ void __launch_bounds__(BS) row_kernel(RowArgs<T> A) {
   } else if (has_inverse) {
     // G_j[m] = GE + GO, G_j'[m] = GE - GO; Z[m] = G_j[m] + i G_j'[m] and its
     // Hermitian mirror Z[N-m] = conj(G_j[m]) + i conj(G_j'[m]); zero elsewhere.
-    for (int idx = tid; idx < RPW * (N - 2 * L + 1); idx += bs) {
-      const int pr = idx / (N - 2 * L + 1), c = L + idx % (N - 2 * L + 1);
-      buf0[pr * N + c] = {(T)0, (T)0};
-    }
-    for (int idx = tid; idx < RPW * L; idx += bs) {
-      const int m = idx / RPW, pr = idx - m * RPW;
-      const int jp = jp0 + pr;
-      cpx<T> ge = {(T)0, (T)0}, go = {(T)0, (T)0};
-      if (pr < np) load_spec_pair(A, spec, it, m, jp, ge, go);
-      const bool eq = (jp == nlat - 1 - jp);
+    for (int c = L + tid; c <= N - L; c += bs) buf0[c] = {(T)0, (T)0};
+    for (int m = tid; m < L; m += bs) {
+      cpx<T> ge, go;
+      load_spec_pair(A, spec, it, m, jp, ge, go);
       const cpx<T> a = cadd(ge, go);
       const cpx<T> b = eq ? cpx<T>{(T)0, (T)0} : csub(ge, go);
-      buf0[pr * N + m] = {a.x - b.y, a.y + b.x};                       // a + i b
-      if (m > 0) buf0[pr * N + N - m] = {a.x + b.y, -a.y + b.x};       // conj(a) + i conj(b)
+      buf0[m] = {a.x - b.y, a.y + b.x};                  // a + i b
+      if (m > 0) buf0[N - m] = {a.x + b.y, -a.y + b.x};  // conj(a) + i conj(b)
     }
     __syncthreads();
-    X = fft_any<T, NC, RPW>(buf0, buf1, N, A.fac, A.nfac, tws, (T)1);
+    X = fft_any<T, NC>(buf0, buf1, N, A.fac, A.nfac, tws, (T)1);
   } else {
     __syncthreads();
   }
 
   if (mode == ROW_INV) {
-    for (int idx = tid; idx < np * N; idx += bs) {
-      ROW_PAIR_SETUP(idx)
+    for (int c = tid; c < N; c += bs) {
       const T s = A.wts_out ? aj : (T)1;
-      const cpx<T> z = X[pr * N + c];
+      const cpx<T> z = X[c];
       A.out[r1 + c] = z.x * s;
       if (!eq) A.out[r2 + c] = z.y * s;
     }
@@ -296,7 +269,7 @@ __global__ void __launch_bounds__(BS) row_kernel(RowArgs<T> A) {
   }
 
   double acc0 = 0.0, acc1 = 0.0, acc2 = 0.0;
-  double kmin = INFINITY, kmax = -INFINITY;  // raw heat-kernel outputs of this group
+  double kmin = INFINITY, kmax = -INFINITY;  // raw heat-kernel outputs of this pair
   bool bad = false;
   if (mode == ROW_SINK_U || mode == ROW_CHECK) {
     // u_hat_k = f(p / (g_{k-1} K v_hat_{k-1})); residual of iteration k-1:
@@ -305,9 +278,8 @@ __global__ void __launch_bounds__(BS) row_kernel(RowArgs<T> A) {
     const T* uo = ubuf_of(A, A.k - 1) + I.foff;
     T* un = ubuf_of(A, A.k) + I.foff;
     const bool chk = (A.chk_slot >= 0);
-    for (int idx = tid, e = 0; idx < np * N; idx += bs, ++e) {
-      ROW_PAIR_SETUP(idx)
-      const cpx<T> z = X[pr * N + c];
+    for (int c = tid, e = 0; c < N; c += bs, ++e) {
+      const cpx<T> z = X[c];
       T nv[2];
       for (int rr = 0; rr < (eq ? 1 : 2); ++rr) {
         const long long fidx = (rr ? r2 : r1) + c;
@@ -329,14 +301,13 @@ __global__ void __launch_bounds__(BS) row_kernel(RowArgs<T> A) {
         nv[rr] = u;
         acc0 += I.balanced ? (double)u : (double)aj * (double)pv * gt;
       }
-      if (mode == ROW_SINK_U) X[pr * N + c] = {nv[0], eq ? (T)0 : nv[1]};
+      if (mode == ROW_SINK_U) X[c] = {nv[0], eq ? (T)0 : nv[1]};
     }
   } else if (mode == ROW_SINK_V) {
     // v_hat_k = f(q / K u_hat_k): Alg. 1 updates v from u before the gauge step.
     T* vn = vbuf_of(A, A.k) + I.foff;
-    for (int idx = tid, e = 0; idx < np * N; idx += bs, ++e) {
-      ROW_PAIR_SETUP(idx)
-      const cpx<T> z = X[pr * N + c];
+    for (int c = tid, e = 0; c < N; c += bs, ++e) {
+      const cpx<T> z = X[c];
       T nv[2];
       for (int rr = 0; rr < (eq ? 1 : 2); ++rr) {
         const long long fidx = (rr ? r2 : r1) + c;
@@ -353,7 +324,7 @@ __global__ void __launch_bounds__(BS) row_kernel(RowArgs<T> A) {
         if (A.store_field) vn[fidx - I.foff] = v;
         nv[rr] = v;
       }
-      X[pr * N + c] = {nv[0], eq ? (T)0 : nv[1]};
+      X[c] = {nv[0], eq ? (T)0 : nv[1]};
     }
   } else if (mode == ROW_ADJ_START || mode == ROW_ADJ_A || mode == ROW_ADJ_VB) {
     // Reverse sweep of the balanced iteration (see adjoint notes above).
@@ -368,9 +339,8 @@ __global__ void __launch_bounds__(BS) row_kernel(RowArgs<T> A) {
       for (int q = tid; q < h; q += bs) sb += A.adjp[(size_t)it * A.hs + q];
       sbar = (T)block_sum(sb, sh);
     }
-    for (int idx = tid; idx < np * N; idx += bs) {
-      ROW_PAIR_SETUP(idx)
-      const cpx<T> z = (mode == ROW_ADJ_START) ? cpx<T>{(T)0, (T)0} : X[pr * N + c];
+    for (int c = tid; c < N; c += bs) {
+      const cpx<T> z = (mode == ROW_ADJ_START) ? cpx<T>{(T)0, (T)0} : X[c];
       T nv[2];
       for (int rr = 0; rr < (eq ? 1 : 2); ++rr) {
         const long long fidx = (rr ? r2 : r1) + c;
@@ -400,7 +370,7 @@ __global__ void __launch_bounds__(BS) row_kernel(RowArgs<T> A) {
           nv[rr] = -ss * vb * v * v / qv;
         }
       }
-      X[pr * N + c] = {nv[0], eq ? (T)0 : nv[1]};
+      X[c] = {nv[0], eq ? (T)0 : nv[1]};
     }
   } else if (mode == ROW_ADJU_V1 || mode == ROW_ADJU_B || mode == ROW_ADJU_A) {
     // Reverse sweep of the unbalanced iteration (see adjoint notes above).
@@ -419,9 +389,8 @@ __global__ void __launch_bounds__(BS) row_kernel(RowArgs<T> A) {
       sAb = (T)(-gb * G / (2.0 * I.eot * SA));
       sBb = (T)(gb * G / (2.0 * I.eot * SB));
     }
-    for (int idx = tid; idx < np * N; idx += bs) {
-      ROW_PAIR_SETUP(idx)
-      const cpx<T> z = has_inverse ? X[pr * N + c] : cpx<T>{(T)0, (T)0};
+    for (int c = tid; c < N; c += bs) {
+      const cpx<T> z = has_inverse ? X[c] : cpx<T>{(T)0, (T)0};
       T nv[2] = {(T)0, (T)0};
       for (int rr = 0; rr < (eq ? 1 : 2); ++rr) {
         const long long fidx = (rr ? r2 : r1) + c;
@@ -456,15 +425,14 @@ __global__ void __launch_bounds__(BS) row_kernel(RowArgs<T> A) {
           nv[rr] = -lam * uhb * u * pow(u, (T)1 / lam) / pv;
         }
       }
-      X[pr * N + c] = {nv[0], eq ? (T)0 : nv[1]};
+      X[c] = {nv[0], eq ? (T)0 : nv[1]};
     }
   } else {  // ROW_FWD, ROW_INIT: load the input rows
     const T* in = A.in;
-    for (int idx = tid; idx < np * N; idx += bs) {
-      ROW_PAIR_SETUP(idx)
+    for (int c = tid; c < N; c += bs) {
       const T v1 = in ? in[r1 + c] : (T)1;
       const T v2 = eq ? (T)0 : (in ? in[r2 + c] : (T)1);
-      X[pr * N + c] = {v1, v2};
+      X[c] = {v1, v2};
       if (mode == ROW_INIT) {
         for (int rr = 0; rr < (eq ? 1 : 2); ++rr) {
           const long long fidx = (rr ? r2 : r1) + c;
@@ -476,30 +444,28 @@ __global__ void __launch_bounds__(BS) row_kernel(RowArgs<T> A) {
       }
     }
   }
-#undef ROW_PAIR_SETUP
 
   if (bad) sh_bad = 1;
   if (mode == ROW_INIT) {
     acc0 = block_sum(acc0, sh);
     acc1 = block_sum(acc1, sh);
     acc2 = block_sum(acc2, sh);
-    if (tid < np) {
-      double* pr = A.prep + ((size_t)it * A.hs + jp0 + tid) * 4;
-      pr[0] = tid == 0 ? acc0 : 0.0;
-      pr[1] = tid == 0 ? acc1 : 0.0;
-      pr[2] = tid == 0 ? acc2 : 0.0;
+    if (tid == 0) {
+      double* pr = A.prep + ((size_t)it * A.hs + jp) * 4;
+      pr[0] = acc0;
+      pr[1] = acc1;
+      pr[2] = acc2;
     }
   } else if (mode == ROW_ADJ_START || mode == ROW_ADJ_VB || mode == ROW_ADJU_V1) {
     acc0 = block_sum(acc0, sh);
-    if (tid < np) A.adjp[(size_t)it * A.hs + jp0 + tid] = tid == 0 ? acc0 : 0.0;
+    if (tid == 0) A.adjp[(size_t)it * A.hs + jp] = acc0;
     if (mode == ROW_ADJU_V1) return;  // v-bar is consumed pointwise by the next launch
   } else if (mode == ROW_SINK_U || mode == ROW_SINK_V || mode == ROW_CHECK) {
     // residual, kernel range and the half's sum in one block reduction
     __shared__ double sh4[4 * 16];
     double r4[4] = {acc2, kmin, kmax, mode == ROW_SINK_U ? acc0 : acc1};
     block_reduce4(r4, sh4);
-    if (A.chk_slot >= 0 && tid < np)
-      A.rhist[((size_t)it * A.nslot + A.chk_slot) * A.hs + jp0 + tid] = tid == 0 ? r4[0] : 0.0;
+    if (A.chk_slot >= 0 && tid == 0) A.rhist[((size_t)it * A.nslot + A.chk_slot) * A.hs + jp] = r4[0];
     if (mode != ROW_CHECK) {
       const double kmn = r4[1], kmx = r4[2], s = r4[3];
       // fold the previous half-iteration's kernel ratio into the item's running minimum
@@ -507,11 +473,11 @@ __global__ void __launch_bounds__(BS) row_kernel(RowArgs<T> A) {
         if (mode == ROW_SINK_V) kratio_fold(A, it, A.k, 2, sh);
         else if (A.k > 1) kratio_fold(A, it, A.k - 1, 4, sh);
       }
-      if (tid < np) {
-        double* rp = A.red + (((size_t)(A.k & 1) * A.nitems_all + it) * A.hs + jp0 + tid) * RED_SLOTS;
-        rp[mode == ROW_SINK_U ? 0 : 1] = tid == 0 ? s : 0.0;
-        rp[mode == ROW_SINK_U ? 2 : 4] = tid == 0 ? kmn : INFINITY;
-        rp[mode == ROW_SINK_U ? 3 : 5] = tid == 0 ? kmx : -INFINITY;
+      if (tid == 0) {
+        double* rp = A.red + (((size_t)(A.k & 1) * A.nitems_all + it) * A.hs + jp) * RED_SLOTS;
+        rp[mode == ROW_SINK_U ? 0 : 1] = s;
+        rp[mode == ROW_SINK_U ? 2 : 4] = kmn;
+        rp[mode == ROW_SINK_U ? 3 : 5] = kmx;
       }
       if (tid == 0 && sh_bad) atomicMin(&A.brk[it], A.k);
     }
@@ -522,18 +488,14 @@ __global__ void __launch_bounds__(BS) row_kernel(RowArgs<T> A) {
   // forward FFT of the rows now in X, fold, weight, store
   cpx<T>* other = (X == buf0) ? buf1 : buf0;
   cpx<T>* Z = RG ? ring_fft<T>(X, other, N, RG, tws, A.ring_blu, (T)-1)
-                 : fft_any<T, NC, RPW>(X, other, N, A.fac, A.nfac, tws, (T)-1);
+                 : fft_any<T, NC>(X, other, N, A.fac, A.nfac, tws, (T)-1);
   const bool adj = (mode == ROW_ADJ_START || mode == ROW_ADJ_A || mode == ROW_ADJ_VB || mode == ROW_ADJU_B ||
                    mode == ROW_ADJU_A);
   const bool unweighted = (mode == ROW_FWD && !A.wts_in) || adj;
-  for (int idx = tid; idx < np * L; idx += bs) {
-    const int m = idx / np, pr = idx - m * np;
-    const int jp = jp0 + pr;
-    const bool eq = (jp == nlat - 1 - jp);
-    const cpx<T>* Zp = Z + pr * N;
+  for (int m = tid; m < L; m += bs) {
     const int cm = RG ? m % N : m;  // HEALPix rings: order m sits in bin m mod N
-    const cpx<T> a = Zp[cm];
-    cpx<T> b = Zp[(N - cm) % N];
+    const cpx<T> a = Z[cm];
+    cpx<T> b = Z[cm == 0 ? 0 : N - cm];
     b.y = -b.y;
     cpx<T> E, O;
     if (eq) {
@@ -546,12 +508,12 @@ __global__ void __launch_bounds__(BS) row_kernel(RowArgs<T> A) {
       O = csub(x1, x2);
     }
     if (RG) {  // e^{-i m phi0}: the rings' first pixels sit at phi0, not 0
-      cpx<T> e = A.ring_ph[(size_t)jp0 * L + m];
+      cpx<T> e = A.ring_ph[(size_t)jp * L + m];
       e.y = -e.y;
       E = cmul(E, e);
       O = cmul(O, e);
     }
-    const T cw = unweighted ? (T)1 : awl[pr];
+    const T cw = unweighted ? (T)1 : aj;
     cpx<T>* sp = spec + ((size_t)m * h + jp) * 2;
     sp[0] = cscale(E, cw);
     sp[1] = cscale(O, cw);
@@ -568,24 +530,23 @@ __global__ void __launch_bounds__(BS) row_kernel(RowArgs<T> A) {
 // thread after the next barrier), so the kernel has two barriers besides the
 // FFT stages.  Compile-time transform length NC, BS threads per workgroup.
 // ---------------------------------------------------------------------------
-template <typename T, int RPW, int NC, int BS>
+template <typename T, int NC, int BS>
 __global__ void __launch_bounds__(BS) row_sink_kernel(RowArgs<T> A) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   constexpr int N = NC;
   constexpr int NW = BS / 64;
-  constexpr int PER = (RPW * N + BS - 1) / BS;  // columns (of both rows of a pair) per thread
+  constexpr int PER = (N + BS - 1) / BS;  // columns (of both rows of the pair) per thread
   const int L = A.L, h = A.h, nlat = A.nlat;
   cpx<T>* buf0 = reinterpret_cast<cpx<T>*>(smem_raw);
-  cpx<T>* buf1 = buf0 + RPW * N;
-  cpx<T>* twl = buf1 + RPW * N;
+  cpx<T>* buf1 = buf0 + N;
+  cpx<T>* twl = buf1 + N;
   __shared__ double shw[NW][4];   // start: gauge sums (0, 1) and previous-half min/max (2, 3)
   __shared__ double shr[NW][4];   // end: sum, residual, min, max of this half
   __shared__ int sh_bad;
-  __shared__ T awl[RPW];
 
-  const int ngroups = (h + RPW - 1) / RPW;
-  const int jp0 = xcd_row_pair(blockIdx.x, ngroups) * RPW;
-  const int np = min(RPW, h - jp0);
+  const int jp = xcd_row_pair(blockIdx.x, h), j2 = nlat - 1 - jp;
+  const bool eq = (jp == j2);  // the equator row of an odd grid
+  const T aj = A.aw[jp];
   const int it = A.item0 + blockIdx.y;
   const ItemDev I = A.items[it];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -598,22 +559,18 @@ __global__ void __launch_bounds__(BS) row_sink_kernel(RowArgs<T> A) {
   T* outf = (umode ? ubuf_of(A, A.k) : vbuf_of(A, A.k)) + I.foff;
   const bool gsum = umode && !A.gk && A.k > 1;       // gauge from the previous iteration's partials
   const bool kfold = A.kr && blockIdx.x == 0 && (!umode || A.k > 1);
-  if (tid < RPW) awl[tid] = (tid < np) ? A.aw[jp0 + tid] : (T)0;
   if (tid == 0) sh_bad = 0;
 
-  // Every global load of the group is issued before anything waits on one:
-  // unconditional loads at in-bounds addresses into registers (entries the
-  // group does not own are loaded from a valid row and never used), then the
-  // LDS writes.  A load under a branch makes the join wait for it, which
+  // Every global load of the pair is issued before anything waits on one:
+  // unconditional loads at in-bounds addresses into registers (columns beyond
+  // the row are loaded from a valid one and never used), then the LDS writes.  A load under a branch makes the join wait for it, which
   // chained the loads into one memory round trip each.
-  // (1) field values for the pointwise step (pairs beyond np and the
-  // equator's second row are skipped there)
+  // (1) field values for the pointwise step (the equator's second row is skipped
+  // there)
   T fv[PER][2], uv[PER][2];
 #pragma unroll
   for (int e = 0; e < PER; ++e) {
-    const int idx = tid + e * BS;
-    const int pr = min(idx / N, np - 1), c = idx % N;
-    const int jp = jp0 + pr, j2 = nlat - 1 - jp;
+    const int c = min(tid + e * BS, N - 1);
     const long long r1 = I.foff + (long long)jp * N + c, r2 = I.foff + (long long)j2 * N + c;
     fv[e][0] = __builtin_nontemporal_load(F + r1);
     fv[e][1] = __builtin_nontemporal_load(F + r2);
@@ -639,52 +596,43 @@ __global__ void __launch_bounds__(BS) row_sink_kernel(RowArgs<T> A) {
     mn = Rk[(size_t)qp * RED_SLOTS + ks];
     mx = Rk[(size_t)qp * RED_SLOTS + ks + 1];
   }
-  // (3) twiddles and the pairs' spectral entries (L <= (N + 1) / 2 orders)
+  // (3) twiddles and the pair's spectral entries (L <= (N + 1) / 2 orders)
   constexpr int TI = (N + BS - 1) / BS;
-  constexpr int GI = (RPW * ((N + 1) / 2) + BS - 1) / BS;
+  constexpr int GI = ((N + 1) / 2 + BS - 1) / BS;
   cpx<T> twv[TI], ge[GI], go[GI];
 #pragma unroll
   for (int i = 0; i < TI; ++i) twv[i] = A.tw[min(tid + i * BS, N - 1)];
   if (!A.cut) {
 #pragma unroll
     for (int gi = 0; gi < GI; ++gi) {
-      const int idx = tid + gi * BS;
-      const int m = idx / RPW, pr = idx - m * RPW;
-      const bool ok = m < L && pr < np;
-      const cpx<T>* sp = spec + ((size_t)(ok ? m : 0) * h + jp0 + (ok ? pr : 0)) * 2;
+      const int m = tid + gi * BS;
+      const cpx<T>* sp = spec + ((size_t)(m < L ? m : 0) * h + jp) * 2;
       ge[gi] = sp[0];
       go[gi] = sp[1];
     }
   }
-  for (int idx = tid; idx < RPW * (N - 2 * L + 1); idx += BS) {
-    const int pr = idx / (N - 2 * L + 1), c = L + idx % (N - 2 * L + 1);
-    buf0[pr * N + c] = {(T)0, (T)0};
-  }
+  for (int c = L + tid; c <= N - L; c += BS) buf0[c] = {(T)0, (T)0};
 #pragma unroll
   for (int i = 0; i < TI; ++i)
     if (tid + i * BS < N) twl[tid + i * BS] = twv[i];
   // Hermitian spectrum of the pair: Z[m] = G_j[m] + i G_j'[m], Z[N-m] its mirror
-  auto put = [&](int m, int pr, cpx<T> e, cpx<T> o) {
-    const int jp = jp0 + pr;
-    const bool eq = (jp == nlat - 1 - jp);
+  auto put = [&](int m, cpx<T> e, cpx<T> o) {
     const cpx<T> a = cadd(e, o);
     const cpx<T> b = eq ? cpx<T>{(T)0, (T)0} : csub(e, o);
-    buf0[pr * N + m] = {a.x - b.y, a.y + b.x};
-    if (m > 0) buf0[pr * N + N - m] = {a.x + b.y, -a.y + b.x};
+    buf0[m] = {a.x - b.y, a.y + b.x};
+    if (m > 0) buf0[N - m] = {a.x + b.y, -a.y + b.x};
   };
   if (!A.cut) {
 #pragma unroll
     for (int gi = 0; gi < GI; ++gi) {
-      const int idx = tid + gi * BS;
-      const int m = idx / RPW, pr = idx - m * RPW;
-      if (m < L) put(m, pr, pr < np ? ge[gi] : cpx<T>{(T)0, (T)0}, pr < np ? go[gi] : cpx<T>{(T)0, (T)0});
+      const int m = tid + gi * BS;
+      if (m < L) put(m, ge[gi], go[gi]);
     }
   } else {
-    for (int idx = tid; idx < RPW * L; idx += BS) {
-      const int m = idx / RPW, pr = idx - m * RPW;
-      cpx<T> e = {(T)0, (T)0}, o = {(T)0, (T)0};
-      if (pr < np) load_spec_pair(A, spec, it, m, jp0 + pr, e, o);
-      put(m, pr, e, o);
+    for (int m = tid; m < L; m += BS) {
+      cpx<T> e, o;
+      load_spec_pair(A, spec, it, m, jp, e, o);
+      put(m, e, o);
     }
   }
   if (!one_pass)
@@ -718,7 +666,7 @@ __global__ void __launch_bounds__(BS) row_sink_kernel(RowArgs<T> A) {
     shw[wave][3] = mx;
   }
   __syncthreads();
-  cpx<T>* X = fft_any<T, NC, RPW>(buf0, buf1, N, A.fac, A.nfac, twl, (T)1);
+  cpx<T>* X = fft_any<T, NC>(buf0, buf1, N, A.fac, A.nfac, twl, (T)1);
 
   // (4) gauge (every thread combines the wave sums in wave order)
   double g = 1.0;
@@ -742,13 +690,9 @@ __global__ void __launch_bounds__(BS) row_sink_kernel(RowArgs<T> A) {
   bool bad = false;
 #pragma unroll
   for (int e = 0; e < PER; ++e) {
-    const int idx = tid + e * BS;
-    const int pr = idx / N, c = idx - pr * N;
-    if (pr >= np) continue;
-    const int jp = jp0 + pr;
-    const bool eq = (jp == nlat - 1 - jp);
-    const T aj = awl[pr];
-    const cpx<T> z = X[pr * N + c];
+    const int c = tid + e * BS;
+    if (c >= N) continue;
+    const cpx<T> z = X[c];
     T nv[2] = {(T)0, (T)0};
 #pragma unroll
     for (int rr = 0; rr < 2; ++rr) {
@@ -779,10 +723,10 @@ __global__ void __launch_bounds__(BS) row_sink_kernel(RowArgs<T> A) {
         acc += (double)x;
       }
       nv[rr] = x;
-      const int jr = rr ? nlat - 1 - jp : jp;
+      const int jr = rr ? j2 : jp;
       if (A.store_field) __builtin_nontemporal_store(x, outf + (long long)jr * N + c);
     }
-    X[pr * N + c] = {nv[0], nv[1]};
+    X[c] = {nv[0], nv[1]};
   }
   if (umode || !I.balanced) acc = wave_sum(acc);  // balanced V halves keep no sum
   if (chk) acc2 = wave_sum(acc2);
@@ -804,13 +748,11 @@ __global__ void __launch_bounds__(BS) row_sink_kernel(RowArgs<T> A) {
       mn = fmin(mn, shr[w][2]);
       mx = fmax(mx, shr[w][3]);
     }
-    for (int pr = 0; pr < np; ++pr) {
-      double* rp = A.red + (((size_t)(A.k & 1) * A.nitems_all + it) * A.hs + jp0 + pr) * RED_SLOTS;
-      rp[umode ? 0 : 1] = pr == 0 ? s : 0.0;
-      rp[umode ? 2 : 4] = pr == 0 ? mn : INFINITY;
-      rp[umode ? 3 : 5] = pr == 0 ? mx : -INFINITY;
-      if (chk) A.rhist[((size_t)it * A.nslot + A.chk_slot) * A.hs + jp0 + pr] = pr == 0 ? s2 : 0.0;
-    }
+    double* rp = A.red + (((size_t)(A.k & 1) * A.nitems_all + it) * A.hs + jp) * RED_SLOTS;
+    rp[umode ? 0 : 1] = s;
+    rp[umode ? 2 : 4] = mn;
+    rp[umode ? 3 : 5] = mx;
+    if (chk) A.rhist[((size_t)it * A.nslot + A.chk_slot) * A.hs + jp] = s2;
     if (sh_bad) atomicMin(&A.brk[it], A.k);
     if (kfold) {
       double pmn = INFINITY, pmx = -INFINITY;
@@ -824,14 +766,10 @@ __global__ void __launch_bounds__(BS) row_sink_kernel(RowArgs<T> A) {
   }
 
   // (6) forward FFT of the updated rows, fold, weight, store
-  cpx<T>* Z = fft_any<T, NC, RPW>(X, X == buf0 ? buf1 : buf0, N, A.fac, A.nfac, twl, (T)-1);
-  for (int idx = tid; idx < np * L; idx += BS) {
-    const int m = idx / np, pr = idx - m * np;
-    const int jp = jp0 + pr;
-    const bool eq = (jp == nlat - 1 - jp);
-    const cpx<T>* Zp = Z + pr * N;
-    const cpx<T> a = Zp[m];
-    cpx<T> b = Zp[(N - m) % N];
+  cpx<T>* Z = fft_any<T, NC>(X, X == buf0 ? buf1 : buf0, N, A.fac, A.nfac, twl, (T)-1);
+  for (int m = tid; m < L; m += BS) {
+    const cpx<T> a = Z[m];
+    cpx<T> b = Z[m == 0 ? 0 : N - m];
     b.y = -b.y;
     cpx<T> E, O;
     if (eq) {
@@ -843,10 +781,9 @@ __global__ void __launch_bounds__(BS) row_sink_kernel(RowArgs<T> A) {
       E = cadd(x1, x2);
       O = csub(x1, x2);
     }
-    const T cw = awl[pr];
     cpx<T>* sp = spec + ((size_t)m * h + jp) * 2;
-    sp[0] = cscale(E, cw);
-    sp[1] = cscale(O, cw);
+    sp[0] = cscale(E, aj);
+    sp[1] = cscale(O, aj);
   }
 }
 
@@ -1457,9 +1394,7 @@ __global__ void __launch_bounds__(256, IB * C > 6 ? 2 : 3) legendre_split_kernel
         }
       }
       if constexpr (ONE) {  // the block's own rows (rows past the range are zero)
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_lds_sync();
 #pragma unroll
         for (int rr = 0; rr < RB; ++rr)
 #pragma unroll
@@ -2754,18 +2689,8 @@ bool take_launch_events(hipEvent_t* start, hipEvent_t* stop) {
   return *start && *stop;
 }
 
-#define SHOT_LAUNCH(kernel, grid, block, lds, stream, ...)                                         \
-  do {                                                                                             \
-    if (g_ev_start && g_ev_stop) {                                                                 \
-      hipExtLaunchKernelGGL(kernel, grid, block, lds, stream, g_ev_start, g_ev_stop, 0, __VA_ARGS__); \
-    } else {                                                                                       \
-      hipLaunchKernelGGL(kernel, grid, block, lds, stream, __VA_ARGS__);                           \
-    }                                                                                              \
-    g_ev_start = g_ev_stop = nullptr;                                                              \
-  } while (0)
 template <typename T, int NC, int BS = 256>
 static hipError_t launch_rows_nc(const RowArgs<T>& a, int nb, hipStream_t stream) {
-  constexpr int RPW = 1;  // (batches of more pairs run row_wave_kernel)
   dim3 grid(a.h, nb);
   RowArgs<T> b = a;
   // two FFT buffers per pair plus the twiddles, in LDS (ring grids size them
@@ -2773,11 +2698,11 @@ static hipError_t launch_rows_nc(const RowArgs<T>& a, int nb, hipStream_t stream
   // of 1440 or more points, long rings) the dynamic-LDS limit is raised, up
   // to 96 KiB for 2048-point fp64 rows and 160 KiB for rings
   const size_t nbuf = a.ring ? (size_t)a.nbuf : (size_t)a.nlon;
-  const size_t lds = (size_t)(2 * RPW + 1) * nbuf * sizeof(cpx<T>);
+  const size_t lds = (size_t)3 * nbuf * sizeof(cpx<T>);
   static std::atomic<unsigned long long> lds_set{0};
-  hipError_t e = allow_lds(reinterpret_cast<const void*>(&row_kernel<T, RPW, NC, BS>), lds, lds_set);
+  hipError_t e = allow_lds(reinterpret_cast<const void*>(&row_kernel<T, NC, BS>), lds, lds_set);
   if (e != hipSuccess) return e;
-  SHOT_LAUNCH((row_kernel<T, RPW, NC, BS>), grid, dim3(BS), lds, stream, b);
+  SHOT_LAUNCH((row_kernel<T, NC, BS>), grid, dim3(BS), lds, stream, b);
   return hipGetLastError();
 }
 
@@ -2802,7 +2727,7 @@ static hipError_t launch_rows_len(const RowArgs<T>& a, int nb, hipStream_t strea
 template <typename T, int NC, int BS>
 static hipError_t launch_sink(const RowArgs<T>& a, int nb, hipStream_t stream) {
   const size_t lds = (size_t)3 * NC * sizeof(cpx<T>);
-  SHOT_LAUNCH((row_sink_kernel<T, 1, NC, BS>), dim3(a.h, nb), dim3(BS), lds, stream, a);
+  SHOT_LAUNCH((row_sink_kernel<T, NC, BS>), dim3(a.h, nb), dim3(BS), lds, stream, a);
   return hipGetLastError();
 }
 

@@ -1,9 +1,11 @@
 // What the kernel launchers share.
 #pragma once
 
+#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
 #include "per_device.h"
+#include "shot_internal.h"
 
 namespace shot {
 
@@ -28,3 +30,14 @@ inline hipError_t allow_lds(const void* kernel, size_t lds, std::atomic<unsigned
 }
 
 }  // namespace shot
+
+// A launch, between the events set for it, if any (attached to the dispatch itself, so
+// that they time the kernel's execution rather than the gap before it).
+#define SHOT_LAUNCH(kernel, grid, block, lds, stream, ...)                                         \
+  do {                                                                                             \
+    hipEvent_t ev0, ev1;                                                                           \
+    if (shot::take_launch_events(&ev0, &ev1))                                                      \
+      hipExtLaunchKernelGGL(kernel, grid, block, lds, stream, ev0, ev1, 0, __VA_ARGS__);           \
+    else                                                                                           \
+      hipLaunchKernelGGL(kernel, grid, block, lds, stream, __VA_ARGS__);                           \
+  } while (0)

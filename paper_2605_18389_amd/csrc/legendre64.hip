@@ -18,8 +18,6 @@
 // Bound: the table stream for few items (8 bytes per entry against 16 columns of
 // matrix work); beyond about 8 items at L = 360 the float64 matrix rate.
 
-#include <hip/hip_ext.h>
-
 #include "device_common.h"
 #include "launch.h"
 
@@ -28,13 +26,6 @@ namespace shot {
 namespace {
 
 typedef double f64x4_t __attribute__((ext_vector_type(4)));
-
-// Orders a wave's LDS writes before its lanes' later reads.
-__device__ __forceinline__ void wave_sync_lds() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 constexpr int T64_PLD = 68;  // tile row pitch (doubles)
 constexpr int T64_DLD = 20;  // partials and b: row pitch per column
@@ -143,7 +134,7 @@ __global__ void __launch_bounds__(BT) legendre_t64_kernel(LegArgs<double> A) {
       if constexpr (MODE == 2) load_coeff(blk + 1);
     }
     if constexpr (MODE != 2) {
-      wave_sync_lds();
+      wave_lds_sync();
       f64x4_t acc = f64x4_t{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int s = 0; s < 16; ++s)
@@ -207,11 +198,7 @@ hipError_t launch_mode(const LegArgs<double>& a, hipStream_t stream) {
   hipError_t e = allow_lds(reinterpret_cast<const void*>(&legendre_t64_kernel<MODE, BT>), lds, lds_set);
   if (e != hipSuccess) return e;
   dim3 grid(a.L, (a.nb + 7) / 8);
-  hipEvent_t e0, e1;
-  if (take_launch_events(&e0, &e1))
-    hipExtLaunchKernelGGL((legendre_t64_kernel<MODE, BT>), grid, dim3(128 * nc), lds, stream, e0, e1, 0, a);
-  else
-    hipLaunchKernelGGL((legendre_t64_kernel<MODE, BT>), grid, dim3(128 * nc), lds, stream, a);
+  SHOT_LAUNCH((legendre_t64_kernel<MODE, BT>), grid, dim3(128 * nc), lds, stream, a);
   return hipGetLastError();
 }
 
@@ -389,7 +376,7 @@ __global__ void __launch_bounds__(BT, 3) legendre_r64_kernel(LegArgs<T> A) {
     load_b(next);
 #pragma unroll
     for (int k = 0; k < 16; ++k) Pt[r64_pos(k) * R64_PLD + lane] = v[k];
-    wave_sync_lds();
+    wave_lds_sync();
     double pa[2][4];
     f64x4_t acc = f64x4_t{0.0, 0.0, 0.0, 0.0};
     auto frag = [&](double* p, int q) {
@@ -472,11 +459,7 @@ hipError_t launch_r64_mode(const LegArgs<T>& a, hipStream_t stream) {
   hipError_t e = allow_lds(reinterpret_cast<const void*>(&legendre_r64_kernel<T, MODE, BT>), lds, lds_set);
   if (e != hipSuccess) return e;
   dim3 grid(a.L, (a.nb + 7) / 8);
-  hipEvent_t e0, e1;
-  if (take_launch_events(&e0, &e1))
-    hipExtLaunchKernelGGL((legendre_r64_kernel<T, MODE, BT>), grid, dim3(128 * nc), lds, stream, e0, e1, 0, a);
-  else
-    hipLaunchKernelGGL((legendre_r64_kernel<T, MODE, BT>), grid, dim3(128 * nc), lds, stream, a);
+  SHOT_LAUNCH((legendre_r64_kernel<T, MODE, BT>), grid, dim3(128 * nc), lds, stream, a);
   return hipGetLastError();
 }
 

@@ -29,8 +29,6 @@
 
 #include <algorithm>
 
-#include <hip/hip_ext.h>
-
 #include "device_common.h"
 #include "launch.h"
 
@@ -92,14 +90,6 @@ template <>
 struct RowFac<360, 64> { static constexpr int n = 3, r[4] = {6, 6, 10}; };
 template <>
 struct RowFac<720, 64> { static constexpr int n = 3, r[4] = {12, 12, 5}; };
-
-// Orders the lanes of a wave through LDS: its LDS operations complete in
-// order, so only the compiler has to keep them in place.
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // Stage S of the transform (inverse: radices in reverse order) of one pair in
 // place, lane l of TP.  The first stage's output is stored with one entry of
@@ -994,13 +984,6 @@ static int wave_stride_rt(int nbuf, int pad, int need) {
   return w;
 }
 
-#define ROWW_LAUNCH(kernel, grid, block, lds, stream, arg)                                             \
-  do {                                                                                                 \
-    hipEvent_t e0, e1;                                                                                 \
-    if (take_launch_events(&e0, &e1)) hipExtLaunchKernelGGL(kernel, grid, block, lds, stream, e0, e1, 0, arg); \
-    else hipLaunchKernelGGL(kernel, grid, block, lds, stream, arg);                                     \
-  } while (0)
-
 template <typename T, int NC, int TP, int NPC, int KIND>
 static hipError_t launch_ct(RowArgs<T> a, int nb, int mod, hipStream_t stream) {
   using F = RowFac<NC, TP>;
@@ -1012,7 +995,7 @@ static hipError_t launch_ct(RowArgs<T> a, int nb, int mod, hipStream_t stream) {
   hipError_t e = allow_lds(reinterpret_cast<const void*>(&row_wave_kernel<T, NC, TP, NPC, KIND>), lds, lds_set);
   if (e != hipSuccess) return e;
   dim3 grid((a.h + NPC - 1) / NPC, nb);
-  ROWW_LAUNCH((row_wave_kernel<T, NC, TP, NPC, KIND>), grid, dim3(TP * NPC), lds, stream, a);
+  SHOT_LAUNCH((row_wave_kernel<T, NC, TP, NPC, KIND>), grid, dim3(TP * NPC), lds, stream, a);
   return hipGetLastError();
 }
 
@@ -1024,7 +1007,7 @@ static hipError_t launch_rt(RowArgs<T> a, int nb, int np, hipStream_t stream) {
   hipError_t e = allow_lds(reinterpret_cast<const void*>(&row_wave_kernel<T, 0, TP, 1, KIND>), lds, lds_set);
   if (e != hipSuccess) return e;
   dim3 grid((a.h + np - 1) / np, nb);
-  ROWW_LAUNCH((row_wave_kernel<T, 0, TP, 1, KIND>), grid, dim3(TP * np), lds, stream, a);
+  SHOT_LAUNCH((row_wave_kernel<T, 0, TP, 1, KIND>), grid, dim3(TP * np), lds, stream, a);
   return hipGetLastError();
 }
 
