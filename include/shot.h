@@ -172,8 +172,9 @@ shot_status shot_heat_apply(shot_plan_t plan, const int32_t* grid_of_item, int32
                             const double* t, const void* v, void* out, int32_t transpose,
                             void* stream);
 
-/* shot_heat_apply for callers that cannot allocate device memory (code under
- * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc).
+/* shot_heat_apply for callers that cannot allocate device memory (tight serving
+ * loops, harnesses that forbid hipMalloc).  Like every call of this library it is
+ * refused on a stream under capture (SHOT_E_HIP, before any launch).
  * Same arguments, result and kernels as shot_heat_apply, but the per-call
  * workspace (item descriptors, folded spectra, heat multipliers) lives in a
  * fixed device array of SHOT_NOALLOC_SCRATCH_BYTES that the library holds on

@@ -686,7 +686,10 @@ shot_status upload_items(shot_plan_s* P, const Layout& Lo, const int32_t* grid_o
                          const std::vector<double>& tvals, const std::vector<const void*>& pp,
                          const std::vector<const void*>& qq, Work<T>& W, hipStream_t s) {
   const int nitems = (int)Lo.order.size();
-  // a call cannot be captured: its workspace belongs to the plan, not to a graph
+  // A call cannot be captured: a larger one (below) copies from host memory and waits,
+  // and a replay would write to a workspace that the plan's next call may have moved
+  // (no-allocation calls: that every call on the GPU shares).  Refused before any
+  // launch, so that the capture itself stays valid.
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   HIP_TRY(hipStreamIsCapturing(s, &cap));
   if (cap != hipStreamCaptureStatusNone) return hip_fail(hipErrorStreamCaptureUnsupported, "call under capture", __LINE__);
