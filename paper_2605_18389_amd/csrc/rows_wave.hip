@@ -21,10 +21,10 @@
 // Arithmetic, partial sums and their slots are those of row_kernel; a wave
 // writes its sums at its first pair and the neutral element at the others.
 // Measured per launch (before -> after): Sinkhorn half of 24 items at 360x720
-// 41 -> 32 us (75 MB, 2.4 TB/s), reverse half of 16 items 46 -> 32 us, heat
-// apply rows of 16 items 21 + 28 -> 14 + 11 us; 24 HEALPix items at Nside 64
-// 56 -> 24 us, 4 at Nside 256 161 -> 65 us; one float64 item of 256-point rows
-// 12.8 -> 7.8 us.  What bounds it now: issue (about 3000 instructions per
+// 38 -> 31 us (75 MB, 2.4 TB/s), reverse half of 16 items 46 -> 31 us, both
+// rows of a heat apply of 16 items 50 -> 23 us; 24 HEALPix items at Nside 64
+// 58 -> 26 us, 4 at Nside 256 162 -> 67 us; one float64 item of 256-point rows
+// 12.8 -> 8.6 us.  What bounds it now: issue (about 3000 instructions per
 // 720-point pair) in batches, the launch's own latency for single items.
 
 #include <algorithm>
@@ -509,8 +509,11 @@ struct alignas(16) EO {
 };
 
 // Waves per SIMD a kernel's registers leave room for.  The adjoint kinds hold
-// more fields per column; one wave fewer keeps them out of scratch memory
-// (unbalanced reverse half of 16 HEALPix items at Nside 64: 26.2 -> 23.9 us).
+// more fields per column; one wave fewer keeps all but one of them out of scratch
+// memory.  Mean row launch of a gradient with four waves -> with three, us: 8
+// balanced HEALPix pairs at Nside 64 23.9 -> 22.5, 16 pairs of 192-point rows 15.2 ->
+// 14.4 (unbalanced 16.0 -> 15.6).  Four are better where three leave a small rest to a
+// second round of workgroups: 16 pairs at Nside 64 38.1 -> 40.6.
 constexpr int row_waves(int real_bytes, int nc, int kind) {
   if (real_bytes == 8) return 2;
   if (nc == 720) return kind >= RK_ADJU_B ? 4 : 5;
@@ -1070,7 +1073,7 @@ RowWaveShape row_wave_shape(const RowArgs<T>& a, int nb) {
   const bool pow2 = a.nlon == 64 || a.nlon == 128 || a.nlon == 256 || a.nlon == 512 || (a.nlon == 1024 && pairs >= 1024);
   const bool deg = sizeof(T) == 4 && (a.nlon == 180 || a.nlon == 360 || a.nlon == 720);
   if (!a.ring && !shared && (pow2 || deg)) {
-    // 64 to 1024 points: always (one item of 256 points: 12.8 -> 7.8 us in
+    // 64 to 1024 points: always (one item of 256 points: 12.8 -> 8.6 us in
     // float64; of 1024 points only with many pairs, the run-time form's 256
     // lanes are faster for one item: 15.1 against 16.9 us).  180, 360 and 720
     // points: from 1024 pairs on; below, row_sink_kernel's wide workgroups
