@@ -419,7 +419,7 @@ __device__ __forceinline__ void point(const RowArgs<T>& A, const ItemDev& I, Pai
       // exponent 1/lam of the rounded lam of the forward update x -> x^lam, which it
       // undoes.  u / u^(-eps/tau), with a separately rounded eps/tau, is off in the same
       // direction at every point (gradient of 2 items at Nside 64, tau = 10, error
-      // against float64: 8.1e-6 -> 1.3e-5)
+      // against float64: 8.3e-6 -> 1.3e-5)
       if constexpr (KIND == RK_ADJU_V1) {
         const T v = C.b[rr];
         const T vb = kt;
