@@ -2204,7 +2204,17 @@ legendre_rmma_kernel(LegArgs<T> A) {
     for (int r = tid + 2 * blockDim.x; r <= 32 * nblk; r += blockDim.x)
       cf[r] = (r < nr && r > 0) ? A.rcoef[toff + min(r, nr - 1)] : 0.0;
   }
-  const double seed = j < h ? sd : 0.0;   // lanes past the last latitude run a zero chain
+  // float32 rows run on sqrt(4 pi) P̄, whose degree 0 is 1, and b takes 1/(4 pi) with its
+  // scale: 1/sqrt(4 pi) rounded to float32 (5e-8 off) would scale the operator's constant
+  // mode, the same way in every apply of a solve and its adjoint; with f_00 and b_00
+  // corrected for that, b_00 and its product round where now b_00 alone does (0.42 -> 0.30
+  // ulp of the constant mode; gradients of batches on 5 grids, 4 sets of 12 inputs each: rms
+  // errors against float64 in the geometric mean 0.86 of that).  The row-split kernel runs on P̄ itself: there the
+  // scale costs f_00 a rounding.
+  constexpr bool SCALED = OP == RM_F32 && SRC != RM_TABLE;
+  constexpr double P00 = 0.28209479177387814347;
+  constexpr double rscale = SCALED ? P00 * P00 : 1.0;
+  const double seed = j < h ? (SCALED ? sd / P00 : sd) : 0.0;   // lanes past the last latitude run a zero chain
   Op yb[NKS][2][NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
@@ -2235,12 +2245,8 @@ legendre_rmma_kernel(LegArgs<T> A) {
   // sensitive (gradient of 8 pairs at 360x720, worst of 6 inputs: error against
   // float64 2.0e-5 with f_00 from the float32 products).
   double* zs = reinterpret_cast<double*>(smem_raw + Q.o_z);
-  // The table and the rows below hold P̄_0^0 = 1/sqrt(4 pi) rounded to float32 (5e-8
-  // off, the same way in every apply of a solve and its adjoint): f_00 takes the
-  // exact value, and b_00 the ratio of the two, so that the rounding leaves the
-  // operator's constant mode.  (A recurrence run on sqrt(4 pi) P̄, whose degree 0 is
-  // 1, does the same here, but cost the row-split kernel a rounding of f_00.)
-  constexpr double P00 = 0.28209479177387814347;
+  // A table holds P̄_0^0 rounded to float32: f_00 takes the exact value, and b_00 the
+  // ratio of the two, so that the rounding leaves the operator's constant mode.
   constexpr double p00fix = P00 / (double)(float)P00;
   if constexpr (OP == RM_F32) {
     if (m == 0) {
@@ -2367,7 +2373,7 @@ legendre_rmma_kernel(LegArgs<T> A) {
       const int e = tid + u * (int)blockDim.x, i = e >> 5, rr = e & 31;
       if (e < 8 * NT * 32) {
         const double g = r0 + rr < nr && i < nit ? gld : 0.0;
-        scd[((rr & 1) * 8 * NT + i) * 16 + (rr >> 1)] = g * g * (double)hld[u];
+        scd[((rr & 1) * 8 * NT + i) * 16 + (rr >> 1)] = g * g * rscale * (double)hld[u];
       }
     }
     for (int e = tid + 2 * blockDim.x; e < 8 * NT * 32; e += blockDim.x) {  // one-wave workgroups of 16 items
@@ -2375,7 +2381,7 @@ legendre_rmma_kernel(LegArgs<T> A) {
       const bool ok = r < nr && i < nit;
       const double g = ok ? (SRC == RM_TABLE ? 1.0 : A.rgam[toff + r]) : 0.0;
       const float hv = ok && mode != 0 ? 1.f : ok ? (float)A.hl[(size_t)(A.item0 + c0 / 2 + i) * A.hl_stride + m + r] : 0.f;
-      scd[((rr & 1) * 8 * NT + i) * 16 + (rr >> 1)] = g * g * (double)hv;
+      scd[((rr & 1) * 8 * NT + i) * 16 + (rr >> 1)] = g * g * rscale * (double)hv;
     }
     // wave partials, [wave][parity][column][row of the parity] (rows padded to 20)
 #pragma unroll
@@ -2405,7 +2411,7 @@ legendre_rmma_kernel(LegArgs<T> A) {
       if (OP == RM_F32 && m == 0 && r0 == 0 && par == 0 && q4 == 0) {
         double z = 0.0;
         for (int w = 0; w < nw; ++w) z += zs[w * NC + n];
-        o[0] = (float)(z * P00 * sc[0] * (mode == 0 ? p00fix : 1.0));
+        o[0] = (float)(z * sc[0] * (SCALED ? 1.0 : mode == 0 ? P00 * p00fix : P00));
       }
       if (SRC == RM_TABLE && mode == 1) {
 #pragma unroll

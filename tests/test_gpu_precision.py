@@ -79,6 +79,25 @@ def test_unbalanced_gradient():
     assert _rms(e) < 1.05e-5, _rms(e)
 
 
+@pytest.mark.parametrize("grid", [("gl", 90, 180, 90), ("gl", 112, 225, 109), ("gl", 123, 250, 123)])
+def test_constant_mode_of_a_batch(grid):
+    """A heat apply that leaves the constant mode alone (t = 50), in a tuned batch.  The batch kernel's f_00 is a
+    float64 sum, and its rows run on sqrt(4 pi) P, whose degree 0 is 1: the field is b_00, rounded once, 0.29 ulp rms;
+    the forward rows' errors, averaged over the latitudes, add 0.05 in quadrature.  With a degree 0 of 1 / sqrt(4 pi)
+    the product rounds as well: 0.41 ulp.  512 fields tell 0.35 from either."""
+    announce(f"constant mode of a batch {grid}")
+    import torch
+    P, D = _plans(grid)
+    P.set_tuning(0, 8, 0)
+    fs, e = P.field_size(0), []
+    for k in range(64):
+        x = torch.cat([_field(P, 8 * k + i) for i in range(8)])
+        out = P.heat_apply(x, 50.0).double().reshape(8, fs)[:, 0]
+        ref = D.heat_apply(x.double(), 50.0).reshape(8, fs)[:, 0]
+        e += ((out - ref) / 2.0 ** (torch.floor(torch.log2(ref)) - 23)).tolist()
+    assert _rms(e) < 0.35, _rms(e)
+
+
 @pytest.mark.parametrize("nside", [251, 401, 509])
 def test_rings_of_long_primes(nside):
     """Coefficients beyond the mean on grids whose belt is rings of 4p pixels, p prime: the radix-p stage sums
