@@ -1117,7 +1117,16 @@ RowWaveShape row_wave_shape(const RowArgs<T>& a, int nb) {
   // longer rows (400 points: 15.1 against 11.9) and for large primes.  Rings of more than
   // 128 pixels from 1200 pairs on (Nside 64, a half: 8 items 18.6 us against 16.6 with
   // 256 lanes, 12 items 20.6 against 23.2).
-  const int line = powers && a.nlon > 128 ? 640 : a.nlon > 200 ? 500 : 0;
+  // A prime radix of 7 to 13 beyond 128 points leaves most of 64 lanes idle in its stages:
+  // one wave per pair from 800 pairs on, float64 from 640 (half of 8 fields of 252 points
+  // 15.6 us against 13.4, float64 16.7 against 15.0; 16 of 182 points 16.3 against 14.9; 16 of
+  // 224, 896 pairs, 14.9 against 15.4; float64 16 of 176, 704 pairs, 14.2 against 15.0).
+  // Below, float32 Sinkhorn and balanced reverse halves run on row_kernel (one field of 154
+  // points: 64 lanes 14.9, 256 lanes 12.3, row_kernel 11.4; 8 of 252 15.6, 13.4, 12.2).
+  const bool prime = !a.ring && a.max_prime > 5 && a.max_prime <= 13 && a.nlon > 128 && a.nlon <= 256;
+  const int line = prime ? (sizeof(T) == 4 && !powers ? 800 : 640)
+                         : powers && a.nlon > 128 ? 640 : a.nlon > 200 ? 500 : 0;
+  if (prime && pairs < line && sizeof(T) == 4 && (kind == RK_SINK || kind == RK_ADJ)) return w;
   const bool narrow = a.ring ? (a.nlon <= 128 || (a.nlon <= 256 && pairs >= 1200))
                              : a.max_prime <= 13 && a.nlon <= 256 && pairs >= line;
   w.tp = narrow ? 64 : 256;

@@ -60,6 +60,16 @@ def test_float64_powers(grid, items):
     _check(grid, items, "fp64", taus=(math.inf, 1.0), gradient=True)
 
 
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("grid,items", [(("gl", 40, 126, 30), 3), (("gl", 40, 132, 30), 1), (("gl", 40, 132, 30), 31),
+                                        (("gl", 40, 132, 30), 32), (("gl", 39, 154, 30), 40), (("gl", 39, 182, 30), 39),
+                                        (("gl", 20, 198, 20), 2), (("gl", 40, 252, 30), 25), (("gl", 40, 252, 30), 40)])
+def test_prime_radices(grid, items, precision):
+    """Rows with a radix of 7, 11 or 13 below and from the pair counts (640 and 800) of one wave a pair, balanced and
+    unbalanced: in float32 the halves below run on the workgroup kernel, the transforms on 256 lanes."""
+    _check(grid, items, precision, taus=(math.inf, 1.0), gradient=True)
+
+
 def test_balanced_and_unbalanced_on_one_plan():
     """A recorded solve is replayed for calls of its own kind only: the same bits as on a plan of its own."""
     import torch
