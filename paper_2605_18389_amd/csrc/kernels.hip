@@ -1341,6 +1341,26 @@ __global__ void __launch_bounds__(256, IB * C > 6 ? 2 : 3) legendre_split_kernel
       R1[c] = v.x;
       R2[c] = v.y;
     }
+    // f_00 of float32 plans: its error is an offset of the whole field, so its lane sums stay
+    // float64 (through the float32 tree below, fields of mean 1 came out 5e-8 off, as
+    // sqrt(4 pi) rounds).  One wave of a launch does this, before its loop: beside the tree,
+    // with the block's sums live, it cost the kernel up to 18 registers.
+    const bool mean = sizeof(T) == 4 && m == 0 && from_seed && r_lo < r_hi;
+    if (mean) {
+#pragma unroll
+      for (int i = 0; i < IB; ++i) {
+        double z = 0.0;
+#pragma unroll
+        for (int c = 0; c < C; ++c) z = fma(R1[c], yE[c][i].x, z);
+        z = wave_sum(z) * gm[0];
+        if (lane == 0 && i < nbi) {
+          if (ONE || A.mode == 0)
+            bs[(size_t)i * maxpl].x = z * gm[0] * (double)A.hl[(size_t)(A.item0 + ib0 + i) * A.hl_stride];
+          else
+            A.coeff[A.items[A.item0 + ib0 + i].coff].x = (T)z;
+        }
+      }
+    }
     const int nblk = (r_hi - r_lo + RB - 1) / RB;  // this wave's blocks in a pass
     int left = ONE ? nblk : 2 * nblk;
     constexpr int SH = NV == 32 ? 1 : 2;  // lanes per reduced value after the transpose-reduction
@@ -1381,7 +1401,7 @@ __global__ void __launch_bounds__(256, IB * C > 6 ? 2 : 3) legendre_split_kernel
       const R s = transpose_reduce<R, NV>(red, lane);
       if ((lane & ((1 << SH) - 1)) == 0) {
         const int vv = lane >> SH, comp = vv & 1, i = (vv >> 1) % IB, rr = (vv >> 1) / IB, r = r0 + rr;
-        if (r < r_hi && i < nbi) {
+        if (r < r_hi && i < nbi && !(mean && r + comp == 0)) {
           const int q = r - P.r_lo;
           const double g = gm[q];
           if (ONE || A.mode == 0) {

@@ -98,6 +98,24 @@ def test_constant_mode_of_a_batch(grid):
     assert _rms(e) < 0.35, _rms(e)
 
 
+@pytest.mark.parametrize("grid,items", [(("gl", 90, 180, 90), 1), (("gl", 40, 80, 40), 2), (("gl", 200, 400, 200), 1),
+                                        (("gl", 200, 400, 200), 2), (("cc", 721, 1440, 720), 1)])
+def test_constant_mode_of_few_fields(grid, items):
+    """As above for the row-split kernel, in its one-pass and two-pass forms: its rows, b and synthesis sums are
+    float64, so with f_00 summed in float64 the constant mode is rounded once, on its way out.  A float32 tree over
+    the lanes adds roundings of 0.425 u each, half the weight a level up: 0.29 and 0.45 in quadrature, 0.5 ulp."""
+    announce(f"constant mode of few fields {grid} x{items}")
+    import torch
+    P, D = _plans(grid)
+    fs, e = P.field_size(0), []
+    for k in range(192 // items):
+        x = torch.cat([_field(P, items * k + i) for i in range(items)])
+        out = P.heat_apply(x, 50.0).double().reshape(items, fs)[:, 0]
+        ref = D.heat_apply(x.double(), 50.0).reshape(items, fs)[:, 0]
+        e += ((out - ref) / 2.0 ** (torch.floor(torch.log2(ref)) - 23)).tolist()
+    assert _rms(e) < 0.36, _rms(e)
+
+
 @pytest.mark.parametrize("nside", [251, 401, 509])
 def test_rings_of_long_primes(nside):
     """Coefficients beyond the mean on grids whose belt is rings of 4p pixels, p prime: the radix-p stage sums
