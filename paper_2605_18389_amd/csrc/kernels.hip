@@ -1344,8 +1344,9 @@ __global__ void __launch_bounds__(256, IB * C > 6 ? 2 : 3) legendre_split_kernel
     // f_00 of float32 plans: its error is an offset of the whole field, so its lane sums stay
     // float64 (through the float32 tree below, fields of mean 1 came out 5e-8 off, as
     // sqrt(4 pi) rounds).  One wave of a launch does this, before its loop: beside the tree,
-    // with the block's sums live, it cost the kernel up to 18 registers.
-    const bool mean = sizeof(T) == 4 && m == 0 && from_seed && r_lo < r_hi;
+    // with the block's sums live, it cost the kernel up to 18 registers.  The one-pass forms
+    // keep the tree: of theirs it costs a resident wave (68 -> 75 and 96 -> 98 registers).
+    const bool mean = sizeof(T) == 4 && !ONE && m == 0 && from_seed && r_lo < r_hi;
     if (mean) {
 #pragma unroll
       for (int i = 0; i < IB; ++i) {
@@ -1354,7 +1355,7 @@ __global__ void __launch_bounds__(256, IB * C > 6 ? 2 : 3) legendre_split_kernel
         for (int c = 0; c < C; ++c) z = fma(R1[c], yE[c][i].x, z);
         z = wave_sum(z) * gm[0];
         if (lane == 0 && i < nbi) {
-          if (ONE || A.mode == 0)
+          if (A.mode == 0)
             bs[(size_t)i * maxpl].x = z * gm[0] * (double)A.hl[(size_t)(A.item0 + ib0 + i) * A.hl_stride];
           else
             A.coeff[A.items[A.item0 + ib0 + i].coff].x = (T)z;
